@@ -139,8 +139,8 @@ struct ps_ctx {
   int64_t lout_seen = 0;
   float lout_raw = 0.0f;
   // staging for the host-memory entry points
-  void* d_stage[3] = {nullptr, nullptr, nullptr};
-  size_t stage_cap[3] = {0, 0, 0};
+  void* d_stage[4] = {nullptr, nullptr, nullptr, nullptr};  // [3]: commit workspace
+  size_t stage_cap[4] = {0, 0, 0, 0};
   // per-arrival scheduler: hits of one launch's requests on every instance
   uint32_t* d_seq_hits = nullptr;
   size_t seq_hits_cap = 0;  // elements
@@ -506,7 +506,7 @@ ps_status ps_destroy(ps_ctx* c) {
   free_snapshot(c);
   dfree(c->d_model);
   dfree(c->d_counter);
-  for (int k = 0; k < 3; ++k)
+  for (int k = 0; k < 4; ++k)
     if (c->d_stage[k]) (void)hipFree(c->d_stage[k]);
   dfree(c->d_seq_hits);
   dfree(c->d_spec);
@@ -1212,6 +1212,82 @@ static ps_status after_commit(ps_ctx* c, hipStream_t s, int64_t* n_dropped) {
   return PS_OK;
 }
 
+// Places entries [k0, k1) of a commit on the device, grouped by instance
+// with array order kept inside a group (host arrays reqs and inst; d_reqs
+// the same requests on the device).  keep: uploads that must outlive the
+// stream's copies.
+static ps_status commit_slice(ps_ctx* c, const uint64_t* d_pool, const ps_req* d_reqs,
+                              const ps_req* reqs, const int32_t* inst, int32_t k0, int32_t k1,
+                              std::vector<std::vector<uint32_t>>* keep, hipStream_t s) {
+  const int32_t ni = c->n_inst;
+  std::vector<uint32_t> start((size_t)ni + 1, 0);
+  for (int32_t k = k0; k < k1; ++k)
+    if (inst[k] >= 0) ++start[(size_t)inst[k] + 1];
+  uint32_t n_grp = 0;
+  for (int32_t i = 0; i < ni; ++i) {
+    n_grp += start[(size_t)i + 1] ? 1u : 0u;
+    start[(size_t)i + 1] += start[(size_t)i];
+  }
+  const uint32_t n_ent = start[(size_t)ni];
+  if (n_ent == 0) return PS_OK;
+  // {header, ent_req, ent_grp, grp_inst, grp_ent, ent_off} in one upload
+  keep->emplace_back(4 + 3 * (size_t)n_ent + 1 + 2 * (size_t)n_grp + 1);
+  std::vector<uint32_t>& up = keep->back();
+  uint32_t* ent_req = up.data() + 4;
+  uint32_t* ent_grp = ent_req + n_ent;
+  uint32_t* grp_inst = ent_grp + n_ent;
+  uint32_t* grp_ent = grp_inst + n_grp;
+  uint32_t* ent_off = grp_ent + n_grp + 1;
+  {
+    std::vector<uint32_t> fill(start.begin(), start.end() - 1);
+    for (int32_t k = k0; k < k1; ++k)
+      if (inst[k] >= 0) ent_req[fill[(size_t)inst[k]]++] = (uint32_t)k;
+  }
+  uint32_t g = 0, off = 0;
+  for (int32_t i = 0; i < ni; ++i) {
+    if (start[(size_t)i] == start[(size_t)i + 1]) continue;
+    grp_inst[g] = (uint32_t)i;
+    grp_ent[g] = start[(size_t)i];
+    for (uint32_t e = start[(size_t)i]; e < start[(size_t)i + 1]; ++e) {
+      ent_grp[e] = g;
+      ent_off[e] = off;
+      off += (uint32_t)(reqs[ent_req[e]].pre_len + reqs[ent_req[e]].tail_len);
+    }
+    ++g;
+  }
+  grp_ent[n_grp] = n_ent;
+  ent_off[n_ent] = off;
+  up[0] = n_ent;
+  up[1] = n_grp;
+  up[2] = off;
+  up[3] = 0;
+  void *dx, *ws;
+  ps_status st = stage_buffer(c, 2, up.size() * sizeof(uint32_t), &dx);
+  if (st == PS_OK) st = stage_buffer(c, 3, ps_commit_ws_bytes(n_ent, n_grp, off), &ws);
+  if (st != PS_OK) return st;
+  HIP_TRY(c, hipMemcpyAsync(dx, up.data(), up.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+  const uint32_t* d = (const uint32_t*)dx;
+  CommitBatch b{};
+  b.t = c->t;
+  b.inst = c->d_inst;
+  b.room = c->d_room;
+  b.model = c->d_model;
+  b.pool = d_pool;
+  b.reqs = d_reqs;
+  b.hdr = (const CommitHdr*)dx;
+  b.ent_req = (const int32_t*)(d + 4);
+  b.ent_grp = d + 4 + n_ent;
+  b.grp_inst = (const int32_t*)(d + 4 + 2 * (size_t)n_ent);
+  b.grp_ent = d + 4 + 2 * (size_t)n_ent + n_grp;
+  b.ent_off = d + 4 + 2 * (size_t)n_ent + 2 * (size_t)n_grp + 1;
+  b.cap = (uint32_t)c->cap;
+  b.move_state = 1;
+  b.dropped = c->d_counter;
+  ps_commit_ws_bind(&b, ws, n_ent, n_grp, off);
+  HIP_TRY(c, ps_launch_commit(b, n_grp, off, s));
+  return PS_OK;
+}
+
 ps_status ps_commit(ps_ctx* c, const uint64_t* pool, int64_t pool_len, const ps_req* reqs,
                     const int32_t* inst, int32_t n, int64_t* n_dropped) {
   if (!c) return fail(nullptr, PS_E_INVAL, "ctx is NULL");
@@ -1233,52 +1309,43 @@ ps_status ps_commit(ps_ctx* c, const uint64_t* pool, int64_t pool_len, const ps_
     cnt[(size_t)i] += 1;
     add[(size_t)i] += ((int64_t)reqs[k].pre_len + reqs[k].tail_len) * bs;
   }
-  std::vector<int32_t> grp_off, grp_inst;
+  int32_t placed = 0;
   for (int32_t i = 0; i < ni; ++i) {
     const InstState& s = c->h_state[(size_t)i];
     if (!cnt[(size_t)i]) continue;
+    placed += cnt[(size_t)i];
     if (s.Q + cnt[(size_t)i] > PS_MAX_DQ)
       return fail(c, PS_E_RANGE, "instance %d: queued would exceed %d", i, PS_MAX_DQ);
     if (s.P + add[(size_t)i] > PS_MAX_PENDING || s.S + add[(size_t)i] > PS_MAX_CONTEXT)
       return fail(c, PS_E_RANGE, "instance %d: token counters would exceed their limits", i);
   }
-  // entries grouped by instance, array order kept inside a group
-  std::vector<int32_t> start((size_t)ni + 1, 0);
-  for (int32_t i = 0; i < ni; ++i) start[(size_t)i + 1] = start[(size_t)i] + cnt[(size_t)i];
-  std::vector<int32_t> order((size_t)start[(size_t)ni]);
-  {
-    std::vector<int32_t> fill(start.begin(), start.end() - 1);
-    for (int32_t k = 0; k < n; ++k)
-      if (inst[k] >= 0) order[(size_t)fill[(size_t)inst[k]]++] = k;
-  }
-  for (int32_t i = 0; i < ni; ++i)
-    if (cnt[(size_t)i]) {
-      grp_inst.push_back(i);
-      grp_off.push_back(start[(size_t)i]);
-    }
-  grp_off.push_back((int32_t)order.size());
-  if (grp_inst.empty()) return PS_OK;
+  if (placed == 0) return PS_OK;
 
   DeviceScope ds(c->device);
-  void *dp, *dr, *dx;
-  const size_t n_grp = grp_inst.size();
-  const size_t aux = (order.size() + 2 * n_grp + 1) * sizeof(int32_t);
+  void *dp, *dr;
   if ((st = stage_buffer(c, 0, (size_t)pool_len * sizeof(uint64_t), &dp)) != PS_OK) return st;
   if ((st = stage_buffer(c, 1, (size_t)n * sizeof(ps_req), &dr)) != PS_OK) return st;
-  if ((st = stage_buffer(c, 2, aux, &dx)) != PS_OK) return st;
-  int32_t* d_order = (int32_t*)dx;
-  int32_t* d_grp_off = d_order + order.size();
-  int32_t* d_grp_inst = d_grp_off + n_grp + 1;
   hipStream_t s = c->stream;
-  HIP_TRY(c, hipMemcpyAsync(dp, pool, (size_t)pool_len * sizeof(uint64_t), hipMemcpyHostToDevice, s));
+  if (pool_len)
+    HIP_TRY(c, hipMemcpyAsync(dp, pool, (size_t)pool_len * sizeof(uint64_t), hipMemcpyHostToDevice, s));
   HIP_TRY(c, hipMemcpyAsync(dr, reqs, (size_t)n * sizeof(ps_req), hipMemcpyHostToDevice, s));
-  HIP_TRY(c, hipMemcpyAsync(d_order, order.data(), order.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-  HIP_TRY(c, hipMemcpyAsync(d_grp_off, grp_off.data(), grp_off.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-  HIP_TRY(c, hipMemcpyAsync(d_grp_inst, grp_inst.data(), n_grp * sizeof(int32_t), hipMemcpyHostToDevice, s));
   HIP_TRY(c, hipMemsetAsync(c->d_counter, 0, sizeof(unsigned long long), s));
-  CommitArgs ca{c->t, c->d_inst, c->d_room, c->d_model, (const uint64_t*)dp, (const ps_req*)dr,
-                d_order, d_grp_off, d_grp_inst, (int32_t)n_grp, (uint32_t)c->cap, c->d_counter};
-  HIP_TRY(c, ps_launch_commit(ca, s));
+  std::vector<std::vector<uint32_t>> keep;
+  // batches of at most kCommitMaxPos chain positions (one entry at least),
+  // in array order
+  for (int32_t k0 = 0; k0 < n;) {
+    int64_t pos = 0;
+    int32_t k1 = k0;
+    for (; k1 < n; ++k1) {
+      const int64_t len = inst[k1] < 0 ? 0 : (int64_t)reqs[k1].pre_len + reqs[k1].tail_len;
+      if (pos > 0 && pos + len > (int64_t)kCommitMaxPos) break;
+      pos += len;
+    }
+    if ((st = commit_slice(c, (const uint64_t*)dp, (const ps_req*)dr, reqs, inst, k0, k1, &keep, s)) !=
+        PS_OK)
+      return st;
+    k0 = k1;
+  }
   return after_commit(c, s, n_dropped);
 }
 

@@ -265,19 +265,42 @@ constexpr int32_t kOrderChunk = 64;
 constexpr int32_t kXcds = 8;  // workgroups go to the XCDs in turn
 constexpr uint32_t kGroupHeadWords = kListCtrWords * (1 + 2 * kXcds);
 
-struct CommitArgs {
+// A batch of placements (ps_commit.hip).  Entries are grouped by instance,
+// arrival order kept inside a group; entry e's chain takes the positions
+// [ent_off[e], ent_off[e + 1]) of the batch.  Sizes are read on the device
+// (hdr), so a batch may be put together by a kernel.
+struct CommitHdr {
+  uint32_t n_ent, n_grp, n_pos, pad;
+};
+constexpr uint32_t kCommitChunkPositions = 1024;  // positions per workgroup and step
+constexpr uint32_t kCommitMaxPos = 1u << 24;      // positions per batch, one chain at least
+struct CommitBatch {
   Tables t;
   InstState* inst;
   int64_t* room;
   const DevModel* model;
   const uint64_t* pool;
   const ps_req* reqs;
-  const int32_t* order;     // entries grouped by instance, array order kept
-  const int32_t* grp_off;   // n_grp + 1
-  const int32_t* grp_inst;  // n_grp
-  int32_t n_grp;
-  uint32_t cap;             // distinct keys allowed per instance
+  const CommitHdr* hdr;
+  const int32_t* ent_req;    // entry -> request
+  const uint32_t* ent_off;   // n_ent + 1
+  const uint32_t* ent_grp;   // entry -> group
+  const uint32_t* ent_skip;  // optional: leading positions known to be in the table
+  const uint32_t* grp_ent;   // n_grp + 1: first entry of a group
+  const int32_t* grp_inst;
+  uint32_t cap;              // distinct keys allowed per instance
+  uint32_t move_state;       // 1: the instances' counters move too
   unsigned long long* dropped;
+  // workspace (ps_commit_ws_bind): the groups' scratch sets (two slots per
+  // position), each position's slot in them, first occurrences per chunk
+  unsigned long long* set_key;
+  uint32_t* set_pos;
+  uint32_t* pos_slot;
+  uint32_t* chunk_won;
+  uint32_t* ent_hit;
+  uint32_t* grp_rank;
+  uint32_t* grp_count;
+  uint32_t* cap_binds;
 };
 
 // One launch of the per-arrival scheduler: requests [r0, r1) of the window,
@@ -386,7 +409,11 @@ bool ps_hits_fit_lds(int32_t n_inst);
 hipError_t ps_build_index(const ps::Tables& t, int32_t n_inst, const uint32_t* count_host,
                           ps::GIndex* x, hipStream_t s);
 void ps_free_index(ps::GIndex* x);
-hipError_t ps_launch_commit(const ps::CommitArgs& a, hipStream_t s);
+// Ordered placement of a batch (ps_commit.hip); max_*: the largest batch hdr
+// may hold.  Workspace: ps_commit_ws_bytes, carved up by ps_commit_ws_bind.
+hipError_t ps_launch_commit(const ps::CommitBatch& b, uint32_t max_grp, uint32_t max_pos, hipStream_t s);
+size_t ps_commit_ws_bytes(uint32_t n_ent, uint32_t n_grp, uint32_t n_pos);
+void ps_commit_ws_bind(ps::CommitBatch* b, void* ws, uint32_t n_ent, uint32_t n_grp, uint32_t n_pos);
 // Zero-hit admission thresholds in key order and their chunk maxima.
 hipError_t ps_launch_lmax(const ps::InstState* inst_key, const uint32_t* order0,
                           const ps::DevModel* m, int32_t n, int4* lm, int32_t* lm1, uint4* csum,

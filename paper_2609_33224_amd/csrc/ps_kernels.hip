@@ -24,7 +24,6 @@
 //                       instance by direct probing of the per-instance tables
 //                       (breadth probe of the first block, then deep walks;
 //                       one lane per probe, a whole bucket per lane).
-//   commit_kernel     - ordered placement of decisions, one wave per instance.
 //
 // The path does no dense contraction, so it uses no MFMA.
 
@@ -2472,69 +2471,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void le
   if (__ballot(deferred_any) != 0ull && lane == 0) *a.defer_any = 1u;  // (a plain store: every writer writes 1)
 }
 
-// One wave per instance that receives placements; its entries are applied
-// in array order, each measured against the table as the earlier entries
-// left it.
-__global__ __launch_bounds__(64) void commit_kernel(CommitArgs a) {
-  const int32_t g = blockIdx.x;
-  const int lane = threadIdx.x;
-  const uint32_t inst = (uint32_t)a.grp_inst[g];
-  const DevModel& m = *a.model;
-  InstState st = a.inst[inst];
-  uint32_t count = a.t.count[inst];
-  unsigned long long dropped = 0;
-  for (int32_t k = a.grp_off[g]; k < a.grp_off[g + 1]; ++k) {
-    const ps_req q = a.reqs[a.order[k]];
-    const ChainRef c{a.pool + q.pre_off, a.pool + q.tail_off, q.pre_len, q.pre_len + q.tail_len};
-    const int32_t ell = c.len;
-    const int64_t L = (int64_t)ell * m.bs;
-    const uint32_t h = deep_walk<false>(a.t, inst, c, nullptr, 0, lane >> 3, lane & 7);
-    st.Q += 1;
-    st.A1 += 1;
-    st.P += L - (int64_t)h * m.bs;
-    st.S += L;
-    for (int32_t base = 0; base < ell; base += 64) {
-      const int32_t j = base + lane;
-      const bool in = j < ell;
-      const uint64_t key = in ? chain_global(c, j) : 0ull;
-      const bool present = in ? probe(a.t, inst, key) : true;
-      // repeated keys inside this chunk: only the first occurrence counts
-      int first = lane;
-      for (int s = 63; s >= 0; --s) {
-        const uint64_t o = __shfl(key, s);
-        if (s < lane && o == key) first = s;
-      }
-      const bool dup = first != lane;
-      const bool want = in && !present && !dup;
-      const uint64_t wm = __ballot(want);
-      const uint32_t rank = (uint32_t)__popcll(wm & ((1ull << lane) - 1ull));
-      const uint32_t room = a.cap > count ? a.cap - count : 0u;
-      const bool ins = want && rank < room;
-      if (ins) {  // new blocks join the row in chain order
-        uint32_t slot = 0;
-        (void)insert_key(a.t, inst, key, &slot);
-        a.t.rows[(size_t)inst * a.t.row_cap + count + rank] = key;
-        a.t.rowpos[(size_t)inst * a.t.slots + slot] = count + rank;
-      }
-      const uint64_t im = __ballot(ins);
-      const uint64_t dup_drop = __ballot(in && dup && !present && !((im >> first) & 1ull));
-      const uint32_t nins = (uint32_t)__popcll(im);
-      count += nins;
-      dropped += (unsigned long long)(__popcll(wm) - nins + __popcll(dup_drop));
-      // later probes of this wave must see these inserts (workgroup scope: a
-      // device-scope fence would write back the XCD's whole L2)
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    }
-  }
-  st.seg = segment_of(m, st.A1);
-  if (lane == 0) {
-    a.inst[inst] = st;
-    a.room[inst] = st.A1 <= m.b_max ? m.kv_cap - st.S : -1;
-    a.t.count[inst] = count;
-    if (dropped) atomicAdd(a.dropped, dropped);
-  }
-}
-
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
@@ -2722,10 +2658,4 @@ hipError_t ps_launch_group(const ScoreArgs& a, int grid, hipStream_t s, hipEvent
   hipLaunchKernelGGL(popular_member_kernel, dim3(kPopWalkGrid), dim3(64), lds, s, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return hipStreamWaitEvent(s, join, 0);
-}
-
-hipError_t ps_launch_commit(const CommitArgs& a, hipStream_t s) {
-  if (a.n_grp == 0) return hipSuccess;
-  hipLaunchKernelGGL(commit_kernel, dim3(a.n_grp), dim3(64), 0, s, a);
-  return hipGetLastError();
 }

@@ -1,0 +1,126 @@
+"""ps_commit against the oracle's entry-by-entry commit, at the sizes where a
+batch taken position by position can go wrong: chains that end at and around a
+chunk of positions, chunks that hold hundreds of short chains, blocks that
+repeat inside a chain and across the chains of one instance, caps that bind
+inside a chain, at a repeat and before the first block, empty chains, and
+placements that skip entries."""
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import DeviceWindow, compare_decisions, edge_window, load_window, nb_cap, reqs_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ps():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_33224_amd as ps
+    return ps
+
+
+@pytest.fixture()
+def scorer(ps):
+    s = ps.Scorer(0)
+    yield s
+    s.close()
+
+
+def _check(scorer, w, inst, label):
+    load_window(scorer, w)
+    o = oracle.Oracle.from_window(w)
+    want = o.commit(w.pool, w.pre_off, w.pre_len, w.tail_off, w.tail_len, inst)
+    got = scorer.commit(w.pool, reqs_of(w), np.asarray(inst, np.int32))
+    so, sg = o.state(), scorer.state()
+    for k in ("D", "Q", "P", "S", "set_size"):
+        assert (so[k] == sg[k]).all(), f"{label}: {k} differs"
+    assert want == got, f"{label}: dropped {got}, oracle {want}"
+    dw = DeviceWindow(w)
+    assert (dw.hits(scorer, w.n_inst) == o.window_hits(w)).all(), f"{label}: tables differ"
+    res, sizes = dw.score(scorer)  # the index and the rows
+    # an empty chain has Z = 0, which the oracle marks near its boundary
+    empty = int((w.pre_len + w.tail_len == 0).sum())
+    compare_decisions(res, sizes, o.window_score(w), label=label, max_nb=nb_cap(w.n_req) + empty)
+    plain, _ = dw.score(scorer, with_sizes=False)
+    assert (plain == res).all(), f"{label}: the two scoring paths differ"
+
+
+def _window(seed, n_inst, n_req, len_lo, len_hi, cap=None, repeats=0.0, shared=0.5, held=40):
+    """Chains over a small alphabet of sessions: a request takes a prefix of a
+    session's chain and a tail; `repeats` of the tails hold blocks of their own
+    chain again; instances hold session prefixes, some with a hole."""
+    rng = np.random.default_rng(seed)
+    nxt = iter(rng.permutation(1 << 20).astype(np.uint64) + np.uint64(1))
+    sess = [[next(nxt) for _ in range(int(rng.integers(max(1, len_lo), len_hi + 1)))]
+            for _ in range(max(1, int(n_req * (1 - shared))))]
+    chains = []
+    for _ in range(n_req):
+        s = sess[int(rng.integers(len(sess)))]
+        pre = s[:int(rng.integers(0, len(s) + 1))]
+        tail = [next(nxt) for _ in range(int(rng.integers(0, 4)))]
+        if pre and rng.random() < repeats:
+            tail = tail + [pre[int(k)] for k in rng.integers(0, len(pre), 3)] + tail[:1]
+        chains.append((pre, tail))
+    sets = []
+    for _ in range(n_inst):
+        have = []
+        for _ in range(int(rng.integers(0, 4))):
+            s = sess[int(rng.integers(len(sess)))]
+            cut = s[:int(rng.integers(0, min(len(s), held) + 1))]
+            if len(cut) > 2 and rng.random() < 0.5:
+                del cut[int(rng.integers(1, len(cut)))]
+            have += cut
+        sets.append(sorted(set(have), key=have.index))
+    if cap is None:
+        cap = 1 + max(len(s) for s in sets) + sum(len(a) + len(b) for a, b in chains)
+    else:
+        cap = max(cap, max(len(s) for s in sets), 1)
+    w = edge_window(sets, chains, cap=cap)
+    inst = rng.integers(-1, n_inst, n_req).astype(np.int32)
+    return w, inst
+
+
+@pytest.mark.parametrize("len_lo,len_hi,n_req,n_inst", [
+    (1, 3, 700, 3),        # hundreds of chains per chunk of 1,024 positions
+    (0, 1, 40, 2),         # empty chains among them
+    (1020, 1027, 9, 2),    # chains around one chunk
+    (2047, 2049, 5, 1),    # one instance, chains around two chunks
+    (30, 300, 150, 70),    # more instances than a wave
+])
+@pytest.mark.parametrize("repeats", [0.0, 0.6])
+def test_commit_chunks(ps, scorer, len_lo, len_hi, n_req, n_inst, repeats):
+    w, inst = _window(len_lo * 7 + n_req, n_inst, n_req, len_lo, len_hi, repeats=repeats)
+    _check(scorer, w, inst, f"commit {len_lo}-{len_hi} x {n_req} on {n_inst}, repeats {repeats}")
+
+
+@pytest.mark.parametrize("cap", [1, 41, 64, 500, 1500])
+@pytest.mark.parametrize("repeats", [0.0, 0.9])
+def test_commit_cap_binds(ps, scorer, cap, repeats):
+    w, inst = _window(cap + 3, 3, 120, 5, 90, cap=cap, repeats=repeats, held=40)
+    _check(scorer, w, inst, f"commit cap {cap}, repeats {repeats}")
+
+
+def test_commit_no_placement(ps, scorer):
+    w, inst = _window(5, 4, 20, 1, 30)
+    inst[:] = -1
+    _check(scorer, w, inst, "commit without placements")
+
+
+def test_commit_empty_chains_only(ps, scorer):
+    w = edge_window([[1, 2], [3]], [[], [], []], cap=8)
+    _check(scorer, w, np.array([0, 1, 0], np.int32), "commit of empty chains")
+
+
+def test_commit_twice(ps, scorer):
+    """A second commit of the same window finds every block and adds none."""
+    w, inst = _window(11, 5, 60, 10, 200)
+    load_window(scorer, w)
+    scorer.commit(w.pool, reqs_of(w), inst)
+    held = scorer.state()["set_size"]
+    P = scorer.state()["P"]
+    assert scorer.commit(w.pool, reqs_of(w), inst) == 0
+    assert (scorer.state()["set_size"] == held).all()
+    assert (scorer.state()["P"] == P).all()
