@@ -107,6 +107,7 @@ struct ps_ctx {
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   int num_cus = 0;
   std::string err;
+  DevPool pool;  // snapshot, index and build buffers
   bool loaded = false;
   // snapshot
   int32_t n_inst = 0;
@@ -346,21 +347,9 @@ ps_status check_reqs_host(ps_ctx* c, const uint64_t* pool, int64_t pool_len, con
 }
 
 void free_snapshot(ps_ctx* c) {
-  dfree(c->t.keys);
-  dfree(c->t.count);
-  dfree(c->t.rows);
-  dfree(c->t.rowpos);
-  dfree(c->d_inst);
-  dfree(c->d_room);
-  dfree(c->d_room_sorted);
-  dfree(c->d_order0);
-  dfree(c->d_inst_key);
-  dfree(c->d_rtop);
-  dfree(c->d_lm);
-  dfree(c->d_lm1);
-  dfree(c->d_csum);
-  dfree(c->d_scratch);
-  ps_free_index(&c->x);
+  c->pool.put(c->t.keys, c->t.count, c->t.rows, c->t.rowpos, c->d_inst, c->d_room, c->d_room_sorted,
+              c->d_order0, c->d_inst_key, c->d_rtop, c->d_lm, c->d_lm1, c->d_csum, c->d_scratch);
+  ps_free_index(&c->x, &c->pool);
   c->loaded = false;
 }
 
@@ -592,55 +581,36 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
   int64_t* d_off = nullptr;
   uint64_t* d_blk = nullptr;
   uint32_t *d_won = nullptr, *d_slot = nullptr, *d_rank = nullptr;
-  auto free_build_temps = [&]() {
-    dfree(d_off);
-    dfree(d_blk);
-    dfree(d_won);
-    dfree(d_slot);
-    dfree(d_rank);
-  };
+  auto free_build_temps = [&]() { c->pool.put(d_off, d_blk, d_won, d_slot, d_rank); };
   auto cleanup = [&]() {
     free_build_temps();
-    dfree(fresh.t.keys);
-    dfree(fresh.t.count);
-    dfree(fresh.t.rows);
-    dfree(fresh.t.rowpos);
-    dfree(fresh.d_inst);
-    dfree(fresh.d_room);
-    dfree(fresh.d_room_sorted);
-    dfree(fresh.d_order0);
-    dfree(fresh.d_inst_key);
-    dfree(fresh.d_rtop);
-    dfree(fresh.d_lm);
-    dfree(fresh.d_lm1);
-    dfree(fresh.d_csum);
-    dfree(fresh.d_scratch);
-    ps_free_index(&fresh.x);
-    dfree(d_off);
-    dfree(d_blk);
+    c->pool.put(fresh.t.keys, fresh.t.count, fresh.t.rows, fresh.t.rowpos, fresh.d_inst, fresh.d_room,
+                fresh.d_room_sorted, fresh.d_order0, fresh.d_inst_key, fresh.d_rtop, fresh.d_lm,
+                fresh.d_lm1, fresh.d_csum, fresh.d_scratch);
+    ps_free_index(&fresh.x, &c->pool);
   };
-  hipError_t e = hipMalloc((void**)&fresh.t.keys, tab_bytes);
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.t.count, (size_t)n * sizeof(uint32_t));
+  hipError_t e = c->pool.get(&fresh.t.keys, tab_bytes);
+  if (e == hipSuccess) e = c->pool.get(&fresh.t.count, (size_t)n * sizeof(uint32_t));
   if (e == hipSuccess)
-    e = hipMalloc((void**)&fresh.t.rowpos, (size_t)n * (size_t)slots * sizeof(uint32_t));
+    e = c->pool.get(&fresh.t.rowpos, (size_t)n * (size_t)slots * sizeof(uint32_t));
   if (e == hipSuccess)
-    e = hipMalloc((void**)&fresh.t.rows, (size_t)n * (size_t)fresh.t.row_cap * sizeof(uint64_t));
-  if (e == hipSuccess && n_blk) e = hipMalloc((void**)&d_won, (size_t)n_blk * sizeof(uint32_t));
-  if (e == hipSuccess && n_blk) e = hipMalloc((void**)&d_slot, (size_t)n_blk * sizeof(uint32_t));
-  if (e == hipSuccess && n_blk) e = hipMalloc((void**)&d_rank, (size_t)n_blk * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_inst, (size_t)n * sizeof(InstState));
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_room, (size_t)n * sizeof(int64_t));
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_room_sorted, (size_t)n * sizeof(int64_t));
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_order0, (size_t)n * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_inst_key, (size_t)n * sizeof(InstState));
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_rtop, (size_t)kTopRooms * sizeof(TopRoom));
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_lm, (size_t)n * sizeof(int4));
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_lm1, (size_t)((n + 63) / 64) * sizeof(int32_t));
-  if (e == hipSuccess) e = hipMalloc((void**)&fresh.d_csum, (size_t)((n + 63) / 64) * sizeof(uint4));
+    e = c->pool.get(&fresh.t.rows, (size_t)n * (size_t)fresh.t.row_cap * sizeof(uint64_t));
+  if (e == hipSuccess && n_blk) e = c->pool.get(&d_won, (size_t)n_blk * sizeof(uint32_t));
+  if (e == hipSuccess && n_blk) e = c->pool.get(&d_slot, (size_t)n_blk * sizeof(uint32_t));
+  if (e == hipSuccess && n_blk) e = c->pool.get(&d_rank, (size_t)n_blk * sizeof(uint32_t));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_inst, (size_t)n * sizeof(InstState));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_room, (size_t)n * sizeof(int64_t));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_room_sorted, (size_t)n * sizeof(int64_t));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_order0, (size_t)n * sizeof(uint32_t));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_inst_key, (size_t)n * sizeof(InstState));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_rtop, (size_t)kTopRooms * sizeof(TopRoom));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_lm, (size_t)n * sizeof(int4));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_lm1, (size_t)((n + 63) / 64) * sizeof(int32_t));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_csum, (size_t)((n + 63) / 64) * sizeof(uint4));
   if (e == hipSuccess && rows)
-    e = hipMalloc((void**)&fresh.d_scratch, (size_t)rows * (size_t)n * sizeof(uint16_t));
-  if (e == hipSuccess) e = hipMalloc((void**)&d_off, (size_t)(n + 1) * sizeof(int64_t));
-  if (e == hipSuccess && n_blk) e = hipMalloc((void**)&d_blk, (size_t)n_blk * sizeof(uint64_t));
+    e = c->pool.get(&fresh.d_scratch, (size_t)rows * (size_t)n * sizeof(uint16_t));
+  if (e == hipSuccess) e = c->pool.get(&d_off, (size_t)(n + 1) * sizeof(int64_t));
+  if (e == hipSuccess && n_blk) e = c->pool.get(&d_blk, (size_t)n_blk * sizeof(uint64_t));
   if (e != hipSuccess) {
     cleanup();
     return fail(c, e == hipErrorOutOfMemory ? PS_E_NOMEM : PS_E_DEVICE,
@@ -689,7 +659,7 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
                        sm);
   BuildArgs ba{fresh.t, d_off, d_blk, n, n_blk, c->d_counter, d_won, d_slot, d_rank};
   if (e == hipSuccess) e = ps_launch_build(ba, sm);
-  if (e == hipSuccess) e = ps_exclusive_scan_u32(d_won, d_rank, n_blk, sm);
+  if (e == hipSuccess) e = ps_exclusive_scan_u32(d_won, d_rank, n_blk, &c->pool, sm);
   if (e == hipSuccess) e = ps_launch_rows(ba, sm);
   unsigned long long full = 0;
   if (e == hipSuccess)
@@ -702,7 +672,7 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
   std::vector<uint32_t> hc((size_t)n);
   if (e == hipSuccess)
     e = hipMemcpy(hc.data(), fresh.t.count, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = ps_build_index(fresh.t, n, hc.data(), &fresh.x, sm);
+  if (e == hipSuccess) e = ps_build_index(fresh.t, n, hc.data(), &fresh.x, &c->pool, sm);
   if (e != hipSuccess) {
     cleanup();
     return fail(c, e == hipErrorOutOfMemory ? PS_E_NOMEM : PS_E_DEVICE, "building tables: %s",
@@ -1204,7 +1174,7 @@ static ps_status after_commit(ps_ctx* c, hipStream_t s, int64_t* n_dropped) {
   HIP_TRY(c, hipMemcpy(c->d_order0, o0.data(), o0.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
   const std::vector<InstState> ik = states_in_order(c->h_state, o0);
   HIP_TRY(c, hipMemcpy(c->d_inst_key, ik.data(), ik.size() * sizeof(InstState), hipMemcpyHostToDevice));
-  HIP_TRY(c, ps_build_index(c->t, c->n_inst, c->h_count.data(), &c->x, s));
+  HIP_TRY(c, ps_build_index(c->t, c->n_inst, c->h_count.data(), &c->x, &c->pool, s));
   HIP_TRY(c, hipStreamSynchronize(s));
   const ps_status lst = refresh_lmax(c);
   if (lst != PS_OK) return lst;

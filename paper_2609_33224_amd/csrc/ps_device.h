@@ -4,7 +4,10 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
+
+#include <vector>
 
 #include "packserve.h"
 
@@ -376,12 +379,52 @@ struct BuildArgs {
   uint32_t* rank;            // n_blk: exclusive scan of `won` (global)
 };
 
+// Device memory a context uses again: a snapshot load and an index build take
+// a dozen buffers each and give as many back, and hipMalloc / hipFree cost 78
+// and 108 us a call here (18 of the 30 ms of a load and four commits on a pool
+// of 64).  Idle buffers are kept up to kPoolIdleMax bytes (one snapshot of the
+// largest benchmark window), the oldest going back to the device beyond that
+// or when an allocation fails, all of them at drain().  One pool per context,
+// under the context's rules for threads.  put() waits for the device, as
+// hipFree does, so no stream still reads a buffer that is handed out again.
+class DevPool {
+ public:
+  ~DevPool() { drain(); }
+  hipError_t get(void** out, size_t bytes);
+  template <class T>
+  hipError_t get(T** out, size_t bytes) {
+    return get((void**)out, bytes);
+  }
+  // Gives back every non-null pointer of the list and clears it.
+  template <class... T>
+  void put(T*&... p) {
+    bool any = false;
+    ((any = any || p != nullptr), ...);
+    if (!any) return;
+    (void)hipDeviceSynchronize();
+    (put_idle((void*)p), ...);
+    ((p = nullptr), ...);
+  }
+  void drain();
+
+ private:
+  struct Block {
+    void* p;
+    size_t bytes;
+  };
+  void put_idle(void* p);
+  std::vector<Block> live_, idle_;
+  size_t idle_bytes_ = 0;
+};
+constexpr size_t kPoolIdleMax = (size_t)4 << 30;
+
 }  // namespace ps
 
 // Kernel launchers (ps_kernels.hip).
 hipError_t ps_launch_build(const ps::BuildArgs& a, hipStream_t s);  // slots, won, slot_of
 hipError_t ps_launch_rows(const ps::BuildArgs& a, hipStream_t s);   // rows, rowpos (needs rank)
-hipError_t ps_exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s);
+hipError_t ps_exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, ps::DevPool* pool,
+                                 hipStream_t s);
 // fast: the policy of the four-requests-per-wave scorer (keyed selector,
 // monotone model, no TTFT admission, no set sizes) selects a kernel built
 // for it alone.
@@ -407,8 +450,8 @@ bool ps_hits_fit_lds(int32_t n_inst);
 // Prefix index build (ps_index.hip): from the per-instance tables.  Frees and
 // replaces *x.  count_host: distinct keys per instance.
 hipError_t ps_build_index(const ps::Tables& t, int32_t n_inst, const uint32_t* count_host,
-                          ps::GIndex* x, hipStream_t s);
-void ps_free_index(ps::GIndex* x);
+                          ps::GIndex* x, ps::DevPool* pool, hipStream_t s);
+void ps_free_index(ps::GIndex* x, ps::DevPool* pool);
 // Ordered placement of a batch (ps_commit.hip); max_*: the largest batch hdr
 // may hold.  Workspace: ps_commit_ws_bytes, carved up by ps_commit_ws_bind.
 hipError_t ps_launch_commit(const ps::CommitBatch& b, uint32_t max_grp, uint32_t max_pos, hipStream_t s);

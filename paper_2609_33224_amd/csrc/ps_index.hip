@@ -94,18 +94,65 @@ __global__ void insert_index_kernel(GIndex x, const uint64_t* uk, const uint32_t
   }
 }
 
-template <class T>
-void dfree(T*& p) {
-  if (p) (void)hipFree((void*)p);
-  p = nullptr;
-}
-
 }  // namespace
 
-void ps_free_index(GIndex* x) {
-  dfree(x->ent);
-  dfree(x->holders);
-  dfree(x->bitmaps);
+hipError_t DevPool::get(void** out, size_t bytes) {
+  *out = nullptr;
+  if (bytes == 0) bytes = 1;
+  // the smallest idle buffer that fits and is at most twice as large (or
+  // small anyway)
+  size_t best = idle_.size();
+  for (size_t k = 0; k < idle_.size(); ++k)
+    if (idle_[k].bytes >= bytes && idle_[k].bytes <= 2 * bytes + 65536 &&
+        (best == idle_.size() || idle_[k].bytes < idle_[best].bytes))
+      best = k;
+  if (best < idle_.size()) {
+    const Block b = idle_[best];
+    idle_.erase(idle_.begin() + (long)best);
+    idle_bytes_ -= b.bytes;
+    live_.push_back(b);
+    *out = b.p;
+    return hipSuccess;
+  }
+  hipError_t e = hipMalloc(out, bytes);
+  if (e == hipErrorOutOfMemory && !idle_.empty()) {
+    (void)hipGetLastError();
+    drain();
+    e = hipMalloc(out, bytes);
+  }
+  if (e != hipSuccess) {
+    *out = nullptr;
+    return e;
+  }
+  live_.push_back(Block{*out, bytes});
+  return hipSuccess;
+}
+
+void DevPool::put_idle(void* p) {
+  if (!p) return;
+  for (size_t k = 0; k < live_.size(); ++k) {
+    if (live_[k].p != p) continue;
+    const Block b = live_[k];
+    live_.erase(live_.begin() + (long)k);
+    idle_.push_back(b);
+    idle_bytes_ += b.bytes;
+    break;
+  }
+  while (idle_bytes_ > kPoolIdleMax) {
+    (void)hipFree(idle_.front().p);
+    idle_bytes_ -= idle_.front().bytes;
+    idle_.erase(idle_.begin());
+  }
+}
+
+void DevPool::drain() {
+  for (const Block& b : idle_) (void)hipFree(b.p);
+  idle_.clear();
+  idle_bytes_ = 0;
+}
+
+void ps_free_index(GIndex* x, DevPool* pool) {
+  pool->put(x->ent, x->holders, x->bitmaps);
   x->bmask = 0;
   x->shift = 64;
 }
@@ -117,7 +164,7 @@ void ps_free_index(GIndex* x) {
   } while (0)
 
 hipError_t ps_build_index(const Tables& t, int32_t n_inst, const uint32_t* count_host, GIndex* x,
-                          hipStream_t s) {
+                          DevPool* pool, hipStream_t s) {
   hipError_t e = hipSuccess;
   std::vector<int64_t> base((size_t)n_inst + 1, 0);
   for (int32_t i = 0; i < n_inst; ++i) base[(size_t)i + 1] = base[(size_t)i] + count_host[i];
@@ -139,19 +186,19 @@ hipError_t ps_build_index(const Tables& t, int32_t n_inst, const uint32_t* count
   int64_t buckets = 1;
   int log2b = 0;
 
-  TRY(hipMalloc(&d_base, base.size() * sizeof(int64_t)));
-  TRY(hipMalloc(&d_cursor, (size_t)n_inst * sizeof(unsigned int)));
-  TRY(hipMalloc(&pk, (size_t)nn * sizeof(uint64_t)));
-  TRY(hipMalloc(&sk, (size_t)nn * sizeof(uint64_t)));
-  TRY(hipMalloc(&uk, (size_t)nn * sizeof(uint64_t)));
-  TRY(hipMalloc(&pv, (size_t)nn * sizeof(uint16_t)));
-  TRY(hipMalloc(&sv, (size_t)nn * sizeof(uint16_t)));
-  TRY(hipMalloc(&uc, (size_t)nn * sizeof(uint32_t)));
-  TRY(hipMalloc(&uo, (size_t)nn * sizeof(uint32_t)));
-  TRY(hipMalloc(&pflag, (size_t)nn * sizeof(uint32_t)));
-  TRY(hipMalloc(&prank, (size_t)nn * sizeof(uint32_t)));
-  TRY(hipMalloc(&d_runs, sizeof(int)));
-  TRY(hipMalloc(&d_full, sizeof(unsigned long long)));
+  TRY(pool->get(&d_base, base.size() * sizeof(int64_t)));
+  TRY(pool->get(&d_cursor, (size_t)n_inst * sizeof(unsigned int)));
+  TRY(pool->get(&pk, (size_t)nn * sizeof(uint64_t)));
+  TRY(pool->get(&sk, (size_t)nn * sizeof(uint64_t)));
+  TRY(pool->get(&uk, (size_t)nn * sizeof(uint64_t)));
+  TRY(pool->get(&pv, (size_t)nn * sizeof(uint16_t)));
+  TRY(pool->get(&sv, (size_t)nn * sizeof(uint16_t)));
+  TRY(pool->get(&uc, (size_t)nn * sizeof(uint32_t)));
+  TRY(pool->get(&uo, (size_t)nn * sizeof(uint32_t)));
+  TRY(pool->get(&pflag, (size_t)nn * sizeof(uint32_t)));
+  TRY(pool->get(&prank, (size_t)nn * sizeof(uint32_t)));
+  TRY(pool->get(&d_runs, sizeof(int)));
+  TRY(pool->get(&d_full, sizeof(unsigned long long)));
   TRY(hipMemcpyAsync(d_base, base.data(), base.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
   TRY(hipMemsetAsync(d_cursor, 0, (size_t)n_inst * sizeof(unsigned int), s));
   TRY(hipMemsetAsync(d_runs, 0, sizeof(int), s));
@@ -167,7 +214,7 @@ hipError_t ps_build_index(const Tables& t, int32_t n_inst, const uint32_t* count
     TRY(hipcub::DeviceRunLengthEncode::Encode(nullptr, b2, sk, uk, uc, d_runs, (int)n, s));
     TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, b3, uc, uo, (int)n, s));
     tmp_bytes = std::max(b1, std::max(b2, b3));
-    TRY(hipMalloc(&tmp, tmp_bytes));
+    TRY(pool->get(&tmp, tmp_bytes));
     TRY(hipcub::DeviceRadixSort::SortPairs(tmp, tmp_bytes, pk, sk, pv, sv, (int)n, 0, 64, s));
     TRY(hipcub::DeviceRunLengthEncode::Encode(tmp, tmp_bytes, sk, uk, uc, d_runs, (int)n, s));
     TRY(hipMemcpyAsync(&runs, d_runs, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -195,10 +242,10 @@ hipError_t ps_build_index(const Tables& t, int32_t n_inst, const uint32_t* count
   }
   nx.bmask = (uint32_t)(buckets - 1);
   nx.shift = (uint32_t)(64 - log2b);
-  TRY(hipMalloc(&nx.ent, (size_t)buckets * kSlotsPerBucket * sizeof(IdxEntry)));
+  TRY(pool->get(&nx.ent, (size_t)buckets * kSlotsPerBucket * sizeof(IdxEntry)));
   TRY(hipMemsetAsync(nx.ent, 0, (size_t)buckets * kSlotsPerBucket * sizeof(IdxEntry), s));
   if (n_pop > 0) {
-    TRY(hipMalloc(&nx.bitmaps, (size_t)n_pop * nx.nw * sizeof(uint64_t)));
+    TRY(pool->get(&nx.bitmaps, (size_t)n_pop * nx.nw * sizeof(uint64_t)));
     TRY(hipMemsetAsync(nx.bitmaps, 0, (size_t)n_pop * nx.nw * sizeof(uint64_t), s));
   }
   if (runs > 0) {
@@ -222,40 +269,26 @@ hipError_t ps_build_index(const Tables& t, int32_t n_inst, const uint32_t* count
   nx.holders = sv;
   nx.n_pop = n_pop;
   sv = nullptr;
-  ps_free_index(x);
+  ps_free_index(x, pool);
   *x = nx;
   nx.ent = nullptr;
   nx.bitmaps = nullptr;
 done:
-  if (nx.ent) (void)hipFree(nx.ent);
-  if (nx.bitmaps) (void)hipFree(nx.bitmaps);
-  dfree(d_base);
-  dfree(d_cursor);
-  dfree(pk);
-  dfree(sk);
-  dfree(uk);
-  dfree(pv);
-  dfree(sv);
-  dfree(uc);
-  dfree(uo);
-  dfree(pflag);
-  dfree(prank);
-  dfree(d_runs);
-  dfree(d_full);
-  if (tmp) (void)hipFree(tmp);
+  pool->put(nx.ent, nx.bitmaps, d_base, d_cursor, pk, sk, uk, pv, sv, uc, uo, pflag, prank, d_runs, d_full,
+            tmp);
   return e;
 }
 
-hipError_t ps_exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, hipStream_t s) {
+hipError_t ps_exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, DevPool* pool,
+                                 hipStream_t s) {
   if (n <= 0) return hipSuccess;
   size_t bytes = 0;
   hipError_t e = hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, in, out, (int)n, s);
   if (e != hipSuccess) return e;
   void* tmp = nullptr;
-  e = hipMalloc(&tmp, bytes);
+  e = pool->get(&tmp, bytes);
   if (e != hipSuccess) return e;
   e = hipcub::DeviceScan::ExclusiveSum(tmp, bytes, in, out, (int)n, s);
-  hipError_t e2 = hipStreamSynchronize(s);
-  (void)hipFree(tmp);
-  return e != hipSuccess ? e : e2;
+  pool->put(tmp);
+  return e;
 }
