@@ -148,8 +148,6 @@ struct ps_ctx {
   size_t seq_budget = (size_t)256 << 20;  // bytes of hits per scheduler launch
   // speculative batches (requests per batch; 0: every request scored in full)
   int32_t spec_batch = kSpecBatch;
-  SpecRec* d_spec = nullptr;
-  int32_t spec_cap = 0;                          // records
   unsigned long long* d_seq_stats = nullptr;     // decisions from speculation, scored in full
   // prefix groups of the scored windows: slot keys (tagged with a window
   // generation, so a new window needs no clearing), slot records, and each
@@ -498,7 +496,6 @@ ps_status ps_destroy(ps_ctx* c) {
   for (int k = 0; k < 4; ++k)
     if (c->d_stage[k]) (void)hipFree(c->d_stage[k]);
   dfree(c->d_seq_hits);
-  dfree(c->d_spec);
   dfree(c->d_seq_stats);
   dfree(c->d_gkeys);
   dfree(c->d_grec);
@@ -1325,43 +1322,165 @@ static bool req_ok_host(const ps_req& q, int64_t pool_len) {
          q.tail_len <= pool_len - q.tail_off && (int64_t)q.pre_len + q.tail_len <= PS_MAX_CHAIN;
 }
 
-// Shared body of the per-arrival scheduler and the replay: launches of the
-// hits pass and the single-workgroup scheduler over chunks of requests,
-// then the refresh of the derived data.
+// Algorithm 1 per arrival in batches (ps_schedule.hip); *taken: requests
+// scheduled (all of them, unless the window's chains share blocks in ways
+// that keep the batches short).  d_counter and the statistics start at zero.
+static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len, const ps_req* d_reqs,
+                             int32_t n_req, ps_result* d_out, uint32_t* d_sizes, int32_t* taken,
+                             hipStream_t s) {
+  const int32_t ni = c->n_inst;
+  const uint32_t max_n = (uint32_t)std::max<size_t>(
+      1, std::min<size_t>((size_t)c->spec_batch, c->seq_budget / ((size_t)ni * sizeof(uint32_t))));
+  // the longest chain and the most positions that max_n requests in a row have
+  std::vector<ps_req> reqs((size_t)n_req);
+  HIP_TRY(c, hipMemcpyAsync(reqs.data(), d_reqs, reqs.size() * sizeof(ps_req), hipMemcpyDeviceToHost, s));
+  HIP_TRY(c, hipStreamSynchronize(s));
+  auto len_of = [&](int32_t r) {
+    const ps_req& q = reqs[(size_t)r];
+    return req_ok_host(q, pool_len) ? (int64_t)q.pre_len + q.tail_len : 0;
+  };
+  int64_t longest = 1, run = 0, most = 1;
+  for (int32_t r = 0; r < n_req; ++r) {
+    run += len_of(r) - (r >= (int32_t)max_n ? len_of(r - (int32_t)max_n) : 0);
+    longest = std::max(longest, len_of(r));
+    most = std::max(most, run);
+  }
+  const uint32_t max_pos = (uint32_t)std::max(longest, std::min(most, (int64_t)kCommitMaxPos));
+
+  const size_t hits = (size_t)max_n * sched_row_stride(ni) * sizeof(uint32_t);
+  const size_t ws_commit = ps_commit_ws_bytes(kSpecBatch, kSpecBatch, max_pos);
+  const size_t words = 32 * (size_t)kSpecBatch;  // the arrays of one word per request
+  unsigned char* ws = nullptr;
+  const size_t bytes = 2 * (hits + 256) + kSpecBatch * sizeof(SpecRec) +
+                       (size_t)kSpecBatch * kSpecBatch * sizeof(uint32_t) + words * sizeof(uint32_t) + ws_commit;
+  HIP_TRY(c, c->pool.get(&ws, bytes));
+  struct Give {
+    ps_ctx* c;
+    unsigned char*& p;
+    ~Give() { c->pool.put(p); }
+  } give{c, ws};
+  unsigned char* p = ws;
+  auto take = [&](size_t n) {
+    unsigned char* r = p;
+    p += (n + 255) & ~(size_t)255;
+    return r;
+  };
+  SchedArgs a{};
+  a.t = c->t;
+  a.inst = c->d_inst;
+  a.room = c->d_room;
+  a.model = c->d_model;
+  a.pool = d_pool;
+  a.pool_len = pool_len;
+  a.reqs = d_reqs;
+  a.n_req = n_req;
+  a.n_inst = ni;
+  a.max_n = max_n;
+  a.max_pos = max_pos;
+  a.cap = (uint32_t)c->cap;
+  a.out = d_out;
+  a.sizes = d_sizes;
+  a.stats = c->d_seq_stats;
+  a.hits = (uint32_t*)take(hits);
+  a.work = (uint32_t*)take(hits);
+  a.spec = (SpecRec*)take(kSpecBatch * sizeof(SpecRec));
+  a.lcp = (uint32_t*)take((size_t)kSpecBatch * kSpecBatch * sizeof(uint32_t));
+  uint32_t* w = (uint32_t*)take(words * sizeof(uint32_t));
+  auto word_array = [&](uint32_t n) {
+    uint32_t* r = w;
+    w += (n + 31u) & ~31u;
+    return r;
+  };
+  a.cursor = word_array(1);
+  a.hdr = (SchedHdr*)word_array(4);
+  a.commit_hdr = (CommitHdr*)word_array(4);
+  a.n_work = word_array(1);
+  a.blen = word_array(kSpecBatch);
+  a.zero_at = word_array(kSpecBatch);
+  a.off = word_array(kSpecBatch + 1);
+  a.ent_req = (int32_t*)word_array(kSpecBatch);
+  a.ent_off = word_array(kSpecBatch + 1);
+  a.ent_grp = word_array(kSpecBatch);
+  a.ent_skip = word_array(kSpecBatch);
+  a.grp_ent = word_array(kSpecBatch + 1);
+  a.grp_inst = (int32_t*)word_array(kSpecBatch);
+  CommitBatch b{};
+  b.t = c->t;
+  b.inst = c->d_inst;
+  b.room = c->d_room;
+  b.model = c->d_model;
+  b.pool = d_pool;
+  b.reqs = d_reqs;
+  b.hdr = a.commit_hdr;
+  b.ent_req = a.ent_req;
+  b.ent_off = a.ent_off;
+  b.ent_grp = a.ent_grp;
+  b.ent_skip = a.ent_skip;
+  b.grp_ent = a.grp_ent;
+  b.grp_inst = a.grp_inst;
+  b.cap = (uint32_t)c->cap;
+  b.move_state = 0;  // the decisions moved it
+  b.dropped = c->d_counter;
+  ps_commit_ws_bind(&b, take(ws_commit), kSpecBatch, kSpecBatch, max_pos);
+  a.set_key = b.set_key;
+  a.set_pos = b.set_pos;
+  a.pos_slot = b.pos_slot;
+  HIP_TRY(c, hipMemsetAsync(a.cursor, 0, sizeof(uint32_t), s));
+  // Batches are queued as if each took max_n requests; what a batch left
+  // out is seen in the cursor, and queued again.  Where little is taken, the
+  // window is left to the in-order scheduler.
+  uint32_t done = 0;
+  while (done < (uint32_t)n_req) {
+    const uint32_t left = (uint32_t)n_req - done;
+    const uint32_t rounds = (left + max_n - 1) / max_n;
+    for (uint32_t k = 0; k < rounds; ++k) {
+      HIP_TRY(c, ps_launch_sched_batch(a, s));
+      HIP_TRY(c, ps_launch_commit(b, max_n, max_pos, s));
+    }
+    uint32_t now = 0;
+    HIP_TRY(c, hipMemcpyAsync(&now, a.cursor, sizeof now, hipMemcpyDeviceToHost, s));
+    HIP_TRY(c, hipStreamSynchronize(s));
+    const uint32_t got = now - done;
+    done = now;
+    if (got < left && (uint64_t)got * 8 < (uint64_t)rounds * std::min(max_n, 128u)) break;
+  }
+  *taken = (int32_t)done;
+  return PS_OK;
+}
+
+// Shared body of the per-arrival scheduler and the replay: the batches where
+// the call allows them, else (and for what they leave) launches of the hits
+// pass and the single-workgroup scheduler over chunks of requests; then the
+// refresh of the derived data.
 static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len,
                                 const ps_req* d_reqs, int32_t n_req, const int32_t* d_forced,
                                 ps_result* d_out, uint32_t* d_sizes, int64_t* n_dropped,
                                 hipStream_t s) {
   const int32_t ni = c->n_inst;
+  HIP_TRY(c, hipMemsetAsync(c->d_counter, 0, sizeof(unsigned long long), s));
+  if (!c->d_seq_stats) HIP_TRY(c, hipMalloc(&c->d_seq_stats, 2 * sizeof(unsigned long long)));
+  HIP_TRY(c, hipMemsetAsync(c->d_seq_stats, 0, 2 * sizeof(unsigned long long), s));
+  // Batches: Algorithm 1 with a keyed selector (the Random and H-C-Q choices
+  // are not a least key)
+  const uint32_t sel = c->h_model.sel;
+  const bool spec = !d_forced && c->spec_batch > 0 && sel != PS_SEL_RANDOM && sel != PS_SEL_HCQ;
+  int32_t r_first = 0;
+  if (spec) {
+    const ps_status st = run_batches(c, d_pool, pool_len, d_reqs, n_req, d_out, d_sizes, &r_first, s);
+    if (st != PS_OK) return st;
+  }
   const size_t per_req = (size_t)ni * sizeof(uint32_t);
-  const int32_t chunk = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)n_req, c->seq_budget / per_req));
-  const size_t need = (size_t)chunk * (size_t)ni;
-  if (need > c->seq_hits_cap) {
+  const int32_t chunk = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)(n_req - r_first), c->seq_budget / per_req));
+  if (r_first < n_req && (size_t)chunk * (size_t)ni > c->seq_hits_cap) {
+    const size_t need = (size_t)chunk * (size_t)ni;
     dfree(c->d_seq_hits);
     c->seq_hits_cap = 0;
     HIP_TRY(c, hipMalloc(&c->d_seq_hits, need * sizeof(uint32_t)));
     c->seq_hits_cap = need;
   }
-  HIP_TRY(c, hipMemsetAsync(c->d_counter, 0, sizeof(unsigned long long), s));
   const int threads = kSeqMaxThreads;  // every step of a request uses the whole workgroup
-  // Speculative batches: Algorithm 1 with a keyed selector (the Random and
-  // H-C-Q choices are not a least key, so they are always scored in full)
-  const uint32_t sel = c->h_model.sel;
-  const bool spec = !d_forced && c->spec_batch > 0 && sel != PS_SEL_RANDOM && sel != PS_SEL_HCQ;
-  int32_t step = chunk;
-  if (spec) {
-    step = std::min(chunk, c->spec_batch);
-    if (c->spec_cap < step) {
-      dfree(c->d_spec);
-      c->spec_cap = 0;
-      HIP_TRY(c, hipMalloc(&c->d_spec, (size_t)step * sizeof(SpecRec)));
-      c->spec_cap = step;
-    }
-  }
-  if (!c->d_seq_stats) HIP_TRY(c, hipMalloc(&c->d_seq_stats, 2 * sizeof(unsigned long long)));
-  HIP_TRY(c, hipMemsetAsync(c->d_seq_stats, 0, 2 * sizeof(unsigned long long), s));
-  for (int32_t r0 = 0; r0 < n_req; r0 += step) {
-    const int32_t r1 = std::min(n_req, r0 + step);
+  for (int32_t r0 = r_first; r0 < n_req; r0 += chunk) {
+    const int32_t r1 = std::min(n_req, r0 + chunk);
     ScoreArgs pa{};
     pa.t = c->t;
     pa.x = c->x;
@@ -1378,11 +1497,7 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
     HIP_TRY(c, ps_launch_score(pa, c->hits_in_lds, grid, true, s));
     SeqArgs q{c->t, c->d_inst, c->d_room, c->d_model, d_pool, pool_len, d_reqs, r0, r1, ni,
               c->d_seq_hits, d_forced, d_out, d_sizes, (uint32_t)c->cap, c->d_counter,
-              nullptr, c->d_seq_stats};
-    if (spec) {
-      HIP_TRY(c, ps_launch_spec(q, c->d_spec, s));
-      q.spec = c->d_spec;
-    }
+              spec ? c->d_seq_stats : nullptr};
     HIP_TRY(c, ps_launch_seq(q, threads, s));
   }
   return after_commit(c, s, n_dropped);

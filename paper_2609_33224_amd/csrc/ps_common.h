@@ -495,15 +495,65 @@ __device__ __forceinline__ void stage_model(DevModel& dst, const DevModel* src, 
     reinterpret_cast<uint32_t*>(&dst)[k] = reinterpret_cast<const uint32_t*>(src)[k];
 }
 
+// The model's scalars in registers (uniform, so scalar ones), its segment
+// tables still in LDS: for a kernel whose loop stores to LDS, so that the
+// compiler would read every field again after each store.  Takes the
+// place of a DevModel in the helpers below.
+struct ModelRegs {
+  float a[6];
+  float k1, k2, k3, eta, tau, ttft_floor, lout1;
+  int32_t bs, b_max;
+  int64_t kv_cap;
+  uint32_t flags, sel;
+  int32_t n_seg;
+  const int32_t* seg_ub;
+  const float (*seg)[4];
+};
+__device__ __forceinline__ float uniform_f(float x) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
+}
+__device__ __forceinline__ uint32_t uniform_u(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ ModelRegs model_regs(const DevModel& m) {
+  ModelRegs r;
+  for (int k = 0; k < 6; ++k) r.a[k] = uniform_f(m.a[k]);
+  r.k1 = uniform_f(m.k1);
+  r.k2 = uniform_f(m.k2);
+  r.k3 = uniform_f(m.k3);
+  r.eta = uniform_f(m.eta);
+  r.tau = uniform_f(m.tau);
+  r.ttft_floor = uniform_f(m.ttft_floor);
+  r.lout1 = uniform_f(m.lout1);
+  r.bs = (int32_t)uniform_u((uint32_t)m.bs);
+  r.b_max = (int32_t)uniform_u((uint32_t)m.b_max);
+  r.kv_cap = (int64_t)((uint64_t)uniform_u((uint32_t)((uint64_t)m.kv_cap >> 32)) << 32 | uniform_u((uint32_t)m.kv_cap));
+  r.flags = uniform_u(m.flags);
+  r.sel = uniform_u(m.sel);
+  r.n_seg = (int32_t)uniform_u((uint32_t)m.n_seg);
+  r.seg_ub = m.seg_ub;
+  r.seg = m.seg;
+  return r;
+}
+
+// Workgroup barrier that orders LDS only: memory loads stay in flight across
+// it (__syncthreads waits for every one, and for the stores).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // ------------------------------------------------------------- latency model
+// Token counts (0 <= x < 2^53) as fp32, rounded once: through fp64, which
+// holds them exactly (five instructions; the direct conversion normalises by
+// shifts, about three times as many).
+__device__ __forceinline__ float tok_f(int64_t x) { return (float)(double)x; }
+
 // Eq. 7 with the empirical C and C^2 terms: n new, c cached tokens.
-__device__ __forceinline__ float t_prefill(const DevModel& m, float n, float c) {
+template <class M>
+__device__ __forceinline__ float t_prefill(const M& m, float n, float c) {
   return m.a[0] + n * (m.a[1] + m.a[2] * c + m.a[3] * n) + c * (m.a[4] + m.a[5] * c);
 }
 
 // T_pf(n, L - n) - T_pf(0, L) as a polynomial in n (no cancellation between
 // two large prefill times).
-__device__ __forceinline__ float recompute_raw(const DevModel& m, float n, float L) {
+template <class M>
+__device__ __forceinline__ float recompute_raw(const M& m, float n, float L) {
   return n * (m.k1 + m.k2 * L + m.k3 * n);
 }
 
@@ -516,12 +566,14 @@ struct Lat {
 // median output length, only on a busy instance) and Eq. 4's TTFT with the
 // queue estimate a0 Q + a1 P.
 // Eq. 8's decode-iteration time with the request's L tokens added to S.
-__device__ __forceinline__ float t_iter_of(const DevModel& m, const InstState& st, int64_t L) {
-  const float* sg = m.seg[st.seg];
+template <class M>
+__device__ __forceinline__ float t_iter_of(const M& m, const InstState& st, int64_t L) {
+  const auto& sg = m.seg[st.seg];
   return sg[3] * (sg[0] + sg[1] * (float)st.A1 + sg[2] * (float)(st.S + L));
 }
 
-__device__ __forceinline__ Lat latency(const DevModel& m, const InstState& st, float n, float c,
+template <class M>
+__device__ __forceinline__ Lat latency(const M& m, const InstState& st, float n, float c,
                                        int64_t L) {
   const float tp = t_prefill(m, n, c);
   const float t_iter = t_iter_of(m, st, L);
@@ -544,7 +596,8 @@ __device__ __forceinline__ InstState shfl_state(const InstState& st, int src) {
   return r;
 }
 
-__device__ __forceinline__ bool eligible(const DevModel& m, int32_t A1, int64_t S, int64_t L) {
+template <class M>
+__device__ __forceinline__ bool eligible(const M& m, int32_t A1, int64_t S, int64_t L) {
   return A1 <= m.b_max && S + L <= m.kv_cap;
 }
 
@@ -615,8 +668,8 @@ struct Member {
 // members of C.
 // KEYED: the caller guarantees a keyed selector (D-C-Q, D-Q, D-Q-C) and no
 // TTFT admission, so those branches compile away.
-template <bool KEYED = false, class State>
-__device__ __forceinline__ Member member_with(const DevModel& m, State state, uint32_t v,
+template <bool KEYED = false, class M, class State>
+__device__ __forceinline__ Member member_with(const M& m, State state, uint32_t v,
                                               int64_t L, float Lf, float wmin, float Z, bool kvc,
                                               float slo) {
   Member r{};
@@ -642,8 +695,8 @@ __device__ __forceinline__ Member member(const ScoreArgs& a, const DevModel& m, 
   return member_with(m, [&]() { return a.inst[i]; }, v, L, Lf, wmin, Z, kvc, slo);
 }
 
-template <bool KEYED = false, class State>
-__device__ __forceinline__ void evaluate_with(const DevModel& m, Acc& acc, uint32_t i, uint32_t v,
+template <bool KEYED = false, class M, class State>
+__device__ __forceinline__ void evaluate_with(const M& m, Acc& acc, uint32_t i, uint32_t v,
                                               State state, int64_t L, float Lf, float wmin,
                                               float Z, bool kvc, float slo) {
   const Member mb = member_with<KEYED>(m, state, v, L, Lf, wmin, Z, kvc, slo);
@@ -673,6 +726,12 @@ __device__ __forceinline__ void evaluate(const ScoreArgs& a, const DevModel& m, 
   evaluate_with(m, acc, i, v, [&]() { return a.inst[i]; }, L, Lf, wmin, Z, kvc, slo);
 }
 
+// One wave's share of a workgroup-wide reduction of the per-arrival schedulers.
+struct SeqPart {
+  uint64_t keyT, keyF;
+  uint32_t hroom, nC, nT, wmin, nA, pad;
+};
+
 // The (r + 1)-th output of a SplitMix64 stream seeded with `seed`
 // (Steele, Lea, Flood; Vigna's public-domain reference).
 __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, int64_t r) {
@@ -682,7 +741,8 @@ __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, int64_t r) {
   return z ^ (z >> 31);
 }
 
-__device__ __forceinline__ int32_t segment_of(const DevModel& m, int32_t B) {
+template <class M>
+__device__ __forceinline__ int32_t segment_of(const M& m, int32_t B) {
   for (int32_t s = 0; s < m.n_seg; ++s)
     if (B <= m.seg_ub[s]) return s;
   return m.n_seg - 1;

@@ -318,33 +318,25 @@ constexpr int kSeqU = 4;             // positions per thread in one sweep or ins
 constexpr uint32_t kExtMax = 128;    // hit extensions swept by the workgroup per request
 constexpr int kSeqB = 2;             // instances per thread whose loads are issued together
 
-// Speculative batches of the per-arrival scheduler.  Every request of a
-// batch is first scored in parallel (one workgroup each) against the state
-// at the batch's start; the scheduler workgroup then takes the batch in
-// order and, for each request, re-evaluates only the instances that earlier
-// requests of the batch were placed on (at most one per request, so at most
-// kSpecBatch): when the speculative result settles the decision against the
-// current state, the request is decided from it; otherwise it is scored in
-// full.  A speculative result keeps |A|, |C|, |T|, W_min and the first
-// members of T and of C in the order of their keys.
+// Batches of the per-arrival scheduler (ps_schedule.hip).  Every request of a
+// batch is first scored in parallel (one workgroup each) against the state at
+// the batch's start, keeping |A|, |C|, |T|, W_min and the first members of T
+// and of C in the order of their keys; the requests are then decided in order
+// from that and from the instances that earlier requests of the batch were
+// placed on (at most one per request, so at most kSpecBatch).
 constexpr int kSpecBatch = kSeqMaxThreads;  // requests per batch at most (one thread per changed instance)
 constexpr int kSpecList = 64;               // members of T (and of C) kept per request
 constexpr int kSpecTop = 4;                 // per-thread candidates gathered before the merge
 
-struct alignas(16) SpecEntry {
-  uint64_t key;  // the selector's key (T) or the fallback key (C); the id in bits 0..15
-  uint32_t w;    // the candidate's recomputation penalty W (fp32 bits)
-  uint32_t pad;
-};
-
 struct alignas(16) SpecRec {
   uint32_t nA, nC, nT;
   uint32_t wmin;       // W_min over A (fp32 bits)
-  uint32_t nLT, nLF;   // entries of lt and lf: the first nLT members of T by key (all of T
-                       // when nLT == nT), the first nLF members of C by fallback key
+  uint32_t nLT, nLF;   // entries of lt and lf: the first nLT members of T by the selector's key
+                       // (all of T when nLT == nT), the first nLF members of C by the fallback
+                       // key; the id in a key's bits 0..15
   uint32_t pad[2];
-  SpecEntry lt[kSpecList];
-  SpecEntry lf[kSpecList];
+  uint64_t lt[kSpecList];
+  uint64_t lf[kSpecList];
 };
 
 struct SeqArgs {
@@ -363,8 +355,54 @@ struct SeqArgs {
   uint32_t* sizes;         // optional |A|,|C|,|T| (Algorithm 1 only)
   uint32_t cap;            // distinct keys allowed per instance
   unsigned long long* dropped;
-  const SpecRec* spec;     // speculative results of requests [r0, r1) (null: none)
-  unsigned long long* stats;  // [0] += decisions taken from them, [1] += decisions scored in full
+  unsigned long long* stats;  // optional: [1] += valid requests scored
+};
+
+// One batch of the per-arrival scheduler; the kernels read on the device
+// where it begins (cursor).
+struct SchedHdr {
+  uint32_t r0, n;   // requests [r0, r0 + n) of the window
+  uint32_t n_pos;   // their chain positions
+  uint32_t stop;    // the batch ends before its request `stop`
+};
+constexpr int32_t kSchedRowMax = 4096;  // largest pool whose rows of hits are staged in LDS
+// Words between two requests' rows of hits (16-byte rows).
+__host__ __device__ constexpr uint32_t sched_row_stride(int32_t n_inst) { return ((uint32_t)n_inst + 3u) & ~3u; }
+struct SchedArgs {
+  Tables t;
+  InstState* inst;
+  int64_t* room;
+  const DevModel* model;
+  const uint64_t* pool;
+  int64_t pool_len;
+  const ps_req* reqs;
+  int32_t n_req, n_inst;
+  uint32_t max_n, max_pos;  // requests, and chain positions unless one chain is longer, per batch
+  uint32_t cap;
+  ps_result* out;
+  uint32_t* sizes;
+  unsigned long long* stats;  // [0] += decided from the batch's scores, [1] += scored in full
+  uint32_t* cursor;           // next request of the window
+  SchedHdr* hdr;
+  uint32_t* blen;             // per request of the batch: blocks, ~0 for a malformed descriptor
+  uint32_t* off;              // kSpecBatch + 1: first chain position
+  uint32_t* zero_at;          // first zero hash, or the length
+  uint32_t* hits;             // max_n x n_inst
+  uint32_t* work;             // walks: request << 16 | instance
+  uint32_t* n_work;
+  SpecRec* spec;
+  uint32_t* lcp;              // kSpecBatch x kSpecBatch
+  unsigned long long* set_key;  // the batch's blocks: two slots per position
+  uint32_t* set_pos;
+  uint32_t* pos_slot;
+  // the commit batch (CommitBatch's fields)
+  CommitHdr* commit_hdr;
+  int32_t* ent_req;
+  uint32_t* ent_off;
+  uint32_t* ent_grp;
+  uint32_t* ent_skip;
+  uint32_t* grp_ent;
+  int32_t* grp_inst;
 };
 
 struct BuildArgs {
@@ -474,9 +512,8 @@ hipError_t ps_launch_group(const ps::ScoreArgs& a, int grid, hipStream_t s, hipE
 // Per-arrival scheduler: one workgroup of `threads` (a multiple of 64, at
 // most kSeqMaxThreads) over requests [a.r0, a.r1).
 hipError_t ps_launch_seq(const ps::SeqArgs& a, int threads, hipStream_t s);
-// Speculative scoring of requests [a.r0, a.r1) (one workgroup each) into
-// out[r - a.r0]; a.hits holds their hits at the current state.
-hipError_t ps_launch_spec(const ps::SeqArgs& a, ps::SpecRec* out, hipStream_t s);
+// One batch of the per-arrival scheduler, without its commit.
+hipError_t ps_launch_sched_batch(const ps::SchedArgs& a, hipStream_t s);
 size_t ps_seq_lds_bytes(int32_t n_inst);
 size_t ps_score_lds_bytes(int32_t n_inst);
 // Pools small enough for the scoring kernel to keep rooms, states and
