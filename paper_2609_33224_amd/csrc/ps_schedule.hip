@@ -477,6 +477,7 @@ struct SchedShared {
   uint32_t what[2], cnt[2][6];
   uint64_t t0[2], f0[2];
   InstState st_o[2];
+  uint32_t held_o[2];  // its cached blocks
   uint32_t extra[2];
   SeqPart part[2][kSeqWaves];
   uint32_t lmax[2][kSpecBatch];  // per changed instance: longest common prefix with a request on it
@@ -503,11 +504,11 @@ static_assert(sizeof(SchedShared) + kSchedRowMax / 8 + 2 * 4 * kSchedRowMax <= 6
 //  E  the deciding waves evaluate every changed instance as it is (as it was,
 //     too, for set sizes), with its hit;
 //  C  all of them take the decision, and its owner moves the instance's state.
-// Four staging waves work beside them: during E they put request b + 1's
-// inputs into LDS (loaded during b - 1), load request b + 2's, and find the
-// first listed members of T and C outside the changed instances, with the
-// state of that instance; during C the longest common prefix of request b + 1
-// with the requests on each changed instance.  So a decision waits for no
+// Five staging waves work beside them: during E four put request b + 1's
+// inputs into LDS (loaded during b - 1) and load request b + 2's, and one finds
+// the first listed members of T and C outside the changed instances, with the
+// state of that instance; during C the four take the longest common prefix of
+// request b + 1 with the requests on each changed instance.  So a decision waits for no
 // memory, and what bounds it is the deciding waves' own instruction issue (one
 // wave, four cycles an instruction) and LDS latency: hence the model in scalar
 // registers, ballots instead of reductions, and counts and fallback keys only
@@ -516,7 +517,7 @@ static_assert(sizeof(SchedShared) + kSchedRowMax / 8 + 2 * 4 * kSchedRowMax <= 6
 // When a changed instance's hit moved, W_min changed or a list ran out, the
 // request is scored over all instances (states and hits only: no table is
 // read).
-constexpr int kDecideThreads = 2 * kSeqMaxThreads;
+constexpr int kDecideThreads = 2 * kSeqMaxThreads + 64;
 __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   SchedShared& sh = *reinterpret_cast<SchedShared*>(smem);
@@ -535,6 +536,13 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
     return;
   }
   const bool row_lds = n_inst <= kSchedRowMax;
+
+  auto clear_decision = [&](uint32_t p) {
+    sh.kT[p] = sh.kF[p] = ~0ull;
+    sh.what[p] = 0u;
+    for (int k = 0; k < 6; ++k) sh.cnt[p][k] = 0u;
+    sh.extra[p] = 0u;
+  };
 
   if (threadIdx.x >= NT) {  // ------------------------------- the staging waves
     const int tid = threadIdx.x - NT;
@@ -567,53 +575,60 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
           if (4u * (u * NT + tid) < stride) r[u * NT + tid] = in_row[u];
       }
     };
-    load_inputs(0u);
-    store_inputs(0u);
-    load_inputs(nb > 1u ? 1u : 0u);
+    // a fifth wave looks for the first listed members outside the changed ones
+    const bool finder = wv == nwv;
+    if (!finder) {
+      load_inputs(0u);
+      store_inputs(0u);
+      load_inputs(nb > 1u ? 1u : 0u);
+    }
     __syncthreads();
     for (uint32_t b = 0; b < nb; ++b) {
       const uint32_t p = b & 1u;
       const SchedSlot& in = sh.slot[p];
       const bool valid = sh.blen[b] != ~0u;
       // E
-      if (wv == 3 && valid) {
+      if (finder && valid) {
         const uint32_t s_nLT = uniform_u(in.head[4]), s_nLF = uniform_u(in.head[5]);
         const uint64_t t0 = spec_first_outside(in.lt[lane], s_nLT, dirty, lane);
         const uint64_t f0 = t0 == ~0ull ? spec_first_outside(in.lf[lane], s_nLF, dirty, lane) : ~0ull;
         const uint64_t o0 = t0 != ~0ull ? t0 : f0;
         InstState st{};
-        if (o0 != ~0ull) st = a.inst[o0 & 0xFFFFu];
+        uint32_t held = 0u;
+        if (o0 != ~0ull) {
+          st = a.inst[o0 & 0xFFFFu];
+          held = a.t.count[o0 & 0xFFFFu];
+        }
         if (lane == 0) {
           sh.t0[p] = t0;
           sh.f0[p] = f0;
           sh.st_o[p] = st;
+          sh.held_o[p] = held;
         }
       }
       // (slot and row b + 1 were last read before the barrier that ended b - 1)
-      store_inputs(b + 1u);
-      load_inputs(b + 2u < nb ? b + 2u : nb - 1u);
-      if (valid) {
-        lds_barrier();
-        // C: request b + 1's common prefixes with the requests before b (b's
-        // owner adds b's); request b's are read
-        sh.lmax[p][tid] = 0u;
-        if ((uint32_t)tid < b && sh.mem[tid] != kNone16)
-          atomicMax(&sh.lmax[p ^ 1u][sh.mem[tid]], sh.slot[p ^ 1u].lcp[tid]);
-        lds_barrier();
-        // barriers beyond these: the first of them was the one just passed
-        const uint32_t extra = uniform_u(sh.extra[p]);
-        if (extra && uniform_u(sh.stop)) {
-          __syncthreads();
-          break;
-        }
-        for (uint32_t k = 0; k < extra; ++k) lds_barrier();
-      } else {
-        lds_barrier();
-        sh.lmax[p][tid] = 0u;
-        if ((uint32_t)tid < b && sh.mem[tid] != kNone16)
-          atomicMax(&sh.lmax[p ^ 1u][sh.mem[tid]], sh.slot[p ^ 1u].lcp[tid]);
-        lds_barrier();
+      if (!finder) {
+        store_inputs(b + 1u);
+        load_inputs(b + 2u < nb ? b + 2u : nb - 1u);
       }
+      lds_barrier();
+      // C: request b + 1's common prefixes with the requests before b (b's
+      // owner adds b's); request b's are read
+      if (!finder) {
+        sh.lmax[p][tid] = 0u;
+        if ((uint32_t)tid < b && sh.mem[tid] != kNone16)
+          atomicMax(&sh.lmax[p ^ 1u][sh.mem[tid]], sh.slot[p ^ 1u].lcp[tid]);
+      } else if (lane == 0) {
+        clear_decision(p ^ 1u);  // last read before this request
+      }
+      lds_barrier();
+      // barriers beyond these: the first of them was the one just passed
+      const uint32_t extra = uniform_u(sh.extra[p]);
+      if (extra && uniform_u(sh.stop)) {
+        __syncthreads();
+        break;
+      }
+      for (uint32_t k = 0; k < extra; ++k) lds_barrier();
     }
     for (int k = 0; k < 4; ++k) __syncthreads();  // the deciding waves' last passes
     return;
@@ -627,19 +642,13 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
   sh.blen[tid] = a.blen[tid];
   sh.mem[tid] = (uint16_t)kNone16;
   sh.lmax[0][tid] = sh.lmax[1][tid] = 0u;
-  auto clear_decision = [&](uint32_t p) {
-    sh.kT[p] = sh.kF[p] = ~0ull;
-    sh.what[p] = 0u;
-    for (int k = 0; k < 6; ++k) sh.cnt[p][k] = 0u;
-    sh.extra[p] = 0u;
-  };
   if (tid == 0) {
     sh.stop = 0u;
     clear_decision(0u);
     clear_decision(1u);
   }
   // the k-th changed instance of this thread
-  uint32_t u_my = ~0u, cnt_my = 0u;
+  uint32_t u_my = ~0u, room_my = 0u, cnt_my = 0u;  // room: blocks its cap leaves; cnt: new ones, at most
   InstState so{}, sc{};
   uint32_t n_u = 0u, done = nb, n_fast = 0u, n_full = 0u;
   int pb = 0;
@@ -670,6 +679,7 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
     bool full = false;     // scored over all instances
     uint32_t h_my = 0u, hx_my = 0u;
     InstState st_full{};
+    uint32_t held_full = 0u;
     if (!valid) lds_barrier();
     if (valid) {
       const float Z = recompute_raw(m, Lf, Lf);  // T_pf(L, 0) - T_pf(0, L)
@@ -683,7 +693,8 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
         bool eb = false, ec = false, cb = false, cc = false, tb = false, tc = false;
         uint32_t wb = ~0u;
         if (mine) {
-          const uint32_t lm = sh.lmax[p][tid];
+          // (an instance at its cap takes no blocks, so its hits stay)
+          const uint32_t lm = room_my ? sh.lmax[p][tid] : 0u;
           h_my = hit_of(u_my);
           hx_my = lm > h_my ? lm : h_my;
           eb = eligible(m, so.A1, so.S, L);
@@ -777,7 +788,7 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
         // blocks of it: then the batch ends before this request
         if (tid == 0) sh.extra[p] = 5u;
         if (mine && hx_my > h_my && eligible(m, sc.A1, sc.S, L)) {
-          bool bad = (uint64_t)a.t.count[u_my] + cnt_my > (uint64_t)a.cap;
+          bool bad = cnt_my > room_my;
           if (!bad && (int32_t)hx_my < ell) {
             const ps_req q = a.reqs[h.r0 + b];
             bad = probe(a.t, u_my, chain_global(ChainRef{a.pool + q.pre_off, a.pool + q.tail_off, q.pre_len, ell},
@@ -853,7 +864,10 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
           fl = uniform_u(gT != ~0ull) ? 0u : PS_R_FALLBACK;
           best = (int32_t)(uniform_u((uint32_t)(gT != ~0ull ? gT : gF)) & 0xFFFFu);
           outside = uniform_u(!test_bit(dirty, (uint32_t)best)) != 0u;
-          if (outside) st_full = a.inst[best];
+          if (outside) {
+            st_full = a.inst[best];
+            held_full = a.t.count[best];
+          }
         }
         lds_barrier();  // `outside` read before the owner marks the instance
       }
@@ -874,6 +888,8 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
           u_my = (uint32_t)best;
           so = sc = full ? st_full : sh.st_o[p];
           cnt_my = 0u;
+          const uint32_t held = full ? held_full : sh.held_o[p];
+          room_my = a.cap > held ? a.cap - held : 0u;
           h_my = hit_of((uint32_t)best);
           hx_my = h_my;
           sh.u_id[n_u] = u_my;
@@ -895,18 +911,15 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
           sc.P += L - (int64_t)v * m.bs;
           sc.S += L;
           sc.seg = seg < m.n_seg ? seg : m.n_seg - 1;
-          cnt_my += (uint32_t)ell - h_my;
+          cnt_my += (uint32_t)ell - v;
         }
       }
       if (outside) ++n_u;
     }
-    if (tid == 0) {
-      clear_decision(p ^ 1u);  // last read before this request
-      if (want_sizes) {
-        sh.sz[0][b] = nA;
-        sh.sz[1][b] = nC;
-        sh.sz[2][b] = nT;
-      }
+    if (want_sizes && tid == 0) {
+      sh.sz[0][b] = nA;
+      sh.sz[1][b] = nC;
+      sh.sz[2][b] = nT;
     }
     lds_barrier();
   }
