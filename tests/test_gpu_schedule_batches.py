@@ -1,0 +1,151 @@
+"""The per-arrival scheduler's batches where a batch has to end early or look
+again: chains that hold one block at different positions or behind different
+blocks, repeats inside a chain, zero hashes, caps that bind inside a batch and
+instances that are full from the start, tables with holes behind a common
+prefix, malformed descriptors among the requests, and pools on both sides of
+what the deciding workgroup stages in LDS.  Against the in-order scheduler
+(every request scored in full) byte for byte, and against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import DeviceWindow, compare_sequential, edge_window, load_window, nb_cap, reqs_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ps():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_33224_amd as ps
+    return ps
+
+
+@pytest.fixture()
+def scorer(ps):
+    s = ps.Scorer(0)
+    yield s
+    s.close()
+
+
+def _run(scorer, w, batch, reqs=None):
+    load_window(scorer, w)
+    scorer.set_schedule_speculation(batch)
+    dw = DeviceWindow(w)
+    if reqs is not None:
+        import paper_2609_33224_amd as ps
+        dw.d_reqs = ps.to_device_bytes(reqs)
+    res, sizes, dropped = dw.schedule(scorer)
+    plain = None
+    if batch:
+        load_window(scorer, w)
+        plain = dw.schedule(scorer, with_sizes=False)[0].copy()
+    return res.copy(), sizes.copy(), dropped, scorer.state(), scorer.schedule_stats(), plain
+
+
+def _check(scorer, w, label, reqs=None, follow=True):
+    a, b = _run(scorer, w, 0, reqs), _run(scorer, w, 256, reqs)
+    bad = np.nonzero(a[0] != b[0])[0]
+    assert len(bad) == 0, f"{label}: {len(bad)} differ, first {bad[0]}: {a[0][bad[0]]} {b[0][bad[0]]}"
+    assert (a[1] == b[1]).all(), f"{label}: set sizes"
+    assert a[2] == b[2], f"{label}: dropped {a[2]} {b[2]}"
+    for k in a[3]:
+        assert (a[3][k] == b[3][k]).all(), f"{label}: {k}"
+    assert (b[5] == b[0]).all(), f"{label}: without set sizes"
+    valid = w.n_req if reqs is None else int((b[0]["flags"] != 8).sum())
+    assert sum(b[4]) == valid, f"{label}: {b[4]} of {valid}"
+    if follow and reqs is None:
+        o = oracle.Oracle.from_window(w)
+        od, dropped = o.window_schedule(w, follow=b[0]["instance"])
+        empty = int((w.pre_len + w.tail_len == 0).sum())  # Z = 0: marked near its boundary
+        compare_sequential(b[0], b[1], od, label=label, max_nb=nb_cap(w.n_req) + empty)
+        assert dropped == b[2]
+    return b
+
+
+def _sessions(seed, n_inst, n_req, n_sess, longest, cap=None, holes=0.0, step=24):
+    """Requests that follow their sessions; instances hold prefixes of them,
+    some with a hole, so a table may go on behind a common prefix."""
+    rng = np.random.default_rng(seed)
+    sess = [[(k + 1) * 10**6 + 7 * j for j in range(int(rng.integers(3, longest)))] for k in range(n_sess)]
+    at = [int(rng.integers(0, 10)) for _ in sess]
+    chains = []
+    for r in range(n_req):
+        k = int(rng.integers(n_sess))
+        at[k] = min(len(sess[k]), at[k] + int(rng.integers(0, step)))
+        chains.append((sess[k][:at[k]], [9 * 10**8 + 10 * r + j for j in range(int(rng.integers(0, 3)))]))
+    sets = []
+    for i in range(n_inst):
+        s = sess[int(rng.integers(n_sess))]
+        have = s[:int(rng.integers(0, len(s) + 1))]
+        if len(have) > 4 and rng.random() < holes:
+            cut = int(rng.integers(1, len(have) - 2))
+            have = have[:cut] + have[cut + 2:]
+        sets.append(have)
+    if cap is None:
+        cap = max(len(s) for s in sets) + sum(len(a) + len(b) for a, b in chains) + 1
+    return edge_window(sets, chains, cap=max(cap, max(len(s) for s in sets), 1), eta=0.31)
+
+
+@pytest.mark.parametrize("n_inst,n_req,n_sess", [(1, 300, 5), (2, 257, 3), (65, 600, 40), (300, 513, 200)])
+@pytest.mark.parametrize("holes", [0.0, 1.0])
+def test_batches_follow_sessions(ps, scorer, n_inst, n_req, n_sess, holes):
+    w = _sessions(n_inst + n_req, n_inst, n_req, n_sess, 120, holes=holes)
+    _check(scorer, w, f"sessions {n_inst} x {n_req}, holes {holes}")
+
+
+@pytest.mark.parametrize("cap", [1, 30, 90, 140, 400])
+def test_batches_cap(ps, scorer, cap):
+    _check(scorer, _sessions(cap, 7, 520, 12, 100, cap=cap), f"cap {cap}")
+
+
+@pytest.mark.parametrize("n_inst", [4095, 4096, 4097, 5003])
+def test_batches_pool_sizes(ps, scorer, n_inst):
+    _check(scorer, _sessions(n_inst, n_inst, 270, 60, 60), f"pool {n_inst}", follow=n_inst == 4097)
+
+
+@pytest.mark.parametrize("kind", ["shifted", "behind", "repeats", "all"])
+def test_batches_irregular_chains(ps, scorer, kind):
+    """Blocks that do not name a prefix: batches end before them (or the
+    in-order scheduler takes over), with the same results."""
+    rng = np.random.default_rng(len(kind))
+    base = [1000 + j for j in range(40)]
+    chains = []
+    for r in range(400):
+        own = [10**7 + 100 * r + j for j in range(6)]
+        pre = base[:int(rng.integers(1, 40))]
+        x = rng.random()
+        if kind in ("shifted", "all") and x < 0.1:
+            chains.append((own[:2] + pre, own[2:]))  # the base at other positions
+        elif kind in ("behind", "all") and x < 0.2:
+            chains.append((own[:1] + pre[1:], own[1:]))  # the same positions behind another block
+        elif kind in ("repeats", "all") and x < 0.3:
+            chains.append((pre, own + pre[:3] + own[:2]))
+        else:
+            chains.append((pre, own))
+    sets = [base[:int(rng.integers(0, 40))] for _ in range(9)]
+    _check(scorer, edge_window(sets, chains, cap=9000, eta=0.31), kind)
+
+
+def test_batches_mostly_irregular(ps, scorer):
+    """Every request breaks the batch: the in-order scheduler takes the rest."""
+    chains = [([5000 + (j * 7 + r) % 50 for j in range(20)], [10**6 + r]) for r in range(300)]
+    sets = [[5000 + j for j in range(10)], [], [5003, 5010, 5017]]
+    _check(scorer, edge_window(sets, chains, cap=2000, eta=0.31), "mostly irregular")
+
+
+def test_batches_zero_hashes_and_malformed(ps, scorer):
+    w = _sessions(77, 20, 600, 30, 80)
+    rng = np.random.default_rng(5)
+    for k in rng.integers(0, len(w.pool), 40):
+        w.pool[k] = 0
+    reqs = reqs_of(w)
+    for r in rng.integers(0, 600, 30):
+        reqs["pre_off"][r] = -1
+    for r in rng.integers(0, 600, 10):
+        reqs["tail_len"][r] = len(w.pool) + 1
+    reqs["pre_off"][0] = reqs["pre_off"][255] = reqs["pre_off"][256] = -1
+    b = _check(scorer, w, "zero hashes, malformed", reqs=reqs)
+    assert (b[0]["flags"] == 8).sum() >= 30
