@@ -127,7 +127,7 @@ struct ps_ctx {
   uint4* d_csum = nullptr;           // per 64 positions: least t_iter (A1 > 1, A1 <= 1), largest room
   GIndex x{nullptr, nullptr, nullptr, 0, 0, 64};
   DevModel* d_model = nullptr;
-  unsigned long long* d_counter = nullptr;
+  unsigned long long* d_counter = nullptr;  // a call's count, then its first zero hash
   uint16_t* d_scratch = nullptr;
   int scratch_rows = 0;
   bool hits_in_lds = true;
@@ -339,9 +339,11 @@ ps_status check_reqs_host(ps_ctx* c, const uint64_t* pool, int64_t pool_len, con
     if ((int64_t)q.pre_len + q.tail_len > PS_MAX_CHAIN)
       return fail(c, PS_E_RANGE, "request %d chain longer than %d blocks", r, PS_MAX_CHAIN);
   }
-  for (int64_t k = 0; k < pool_len; ++k)
-    if (pool[k] == 0) return fail(c, PS_E_INVAL, "zero block hash at pool[%lld]", (long long)k);
   return PS_OK;
+}
+
+ps_status zero_hash(ps_ctx* c, const char* what, unsigned long long at) {
+  return fail(c, PS_E_INVAL, "zero block hash at %s[%lld]", what, (long long)at);
 }
 
 void free_snapshot(ps_ctx* c) {
@@ -459,7 +461,7 @@ ps_status ps_create(int device, ps_ctx** out) {
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->fork_ev, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->join_ev, hipEventDisableTiming);
   if (e == hipSuccess) e = hipMalloc((void**)&c->d_model, sizeof(DevModel));
-  if (e == hipSuccess) e = hipMalloc((void**)&c->d_counter, sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipMalloc((void**)&c->d_counter, 2 * sizeof(unsigned long long));
   if (e != hipSuccess) {
     ps_destroy(c);
     return fail(nullptr, PS_E_DEVICE, "device set-up failed: %s", hipGetErrorString(e));
@@ -556,8 +558,6 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
   }
   const int64_t n_blk = in->blk_off[n];
   if (n_blk > 0 && !in->blk) return fail(c, PS_E_INVAL, "blk is NULL");
-  for (int64_t k = 0; k < n_blk; ++k)
-    if (in->blk[k] == 0) return fail(c, PS_E_INVAL, "zero block hash at blk[%lld]", (long long)k);
 
   // geometry: >= 2 * cap slots, power of two buckets of 8 slots
   int64_t slots = 8;
@@ -655,16 +655,23 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
     e = hipMemcpyAsync(fresh.d_rtop, htop.data(), htop.size() * sizeof(TopRoom), hipMemcpyHostToDevice,
                        sm);
   BuildArgs ba{fresh.t, d_off, d_blk, n, n_blk, c->d_counter, d_won, d_slot, d_rank};
+  // zero hashes are looked for on the device, beside the build, which skips
+  // them (6 M hashes take one host thread 2 ms)
+  if (e == hipSuccess) e = ps_launch_first_zero(d_blk, n_blk, c->d_counter + 1, sm);
   if (e == hipSuccess) e = ps_launch_build(ba, sm);
   if (e == hipSuccess) e = ps_exclusive_scan_u32(d_won, d_rank, n_blk, &c->pool, sm);
   if (e == hipSuccess) e = ps_launch_rows(ba, sm);
-  unsigned long long full = 0;
+  unsigned long long found[2] = {0, ~0ull};  // keys without a free slot, first zero hash
   if (e == hipSuccess)
-    e = hipMemcpyAsync(&full, c->d_counter, sizeof full, hipMemcpyDeviceToHost, sm);
+    e = hipMemcpyAsync(found, c->d_counter, sizeof found, hipMemcpyDeviceToHost, sm);
   if (e == hipSuccess) e = hipStreamSynchronize(sm);
-  if (e == hipSuccess && full) {
+  if (e == hipSuccess && found[1] != ~0ull) {
     cleanup();
-    return fail(c, PS_E_DEVICE, "table build found no free slot for %llu keys", full);
+    return zero_hash(c, "blk", found[1]);
+  }
+  if (e == hipSuccess && found[0]) {
+    cleanup();
+    return fail(c, PS_E_DEVICE, "table build found no free slot for %llu keys", found[0]);
   }
   std::vector<uint32_t> hc((size_t)n);
   if (e == hipSuccess)
@@ -1146,12 +1153,16 @@ ps_status ps_score_window(ps_ctx* c, const uint64_t* pool, int64_t pool_len, con
   if (pool_len)
     HIP_TRY(c, hipMemcpyAsync(dp, pool, (size_t)pool_len * sizeof(uint64_t), hipMemcpyHostToDevice, s));
   HIP_TRY(c, hipMemcpyAsync(dr, reqs, (size_t)n_req * sizeof(ps_req), hipMemcpyHostToDevice, s));
+  // (a zero hash ends a walk, so the scoring may run before the check is read)
+  HIP_TRY(c, ps_launch_first_zero((const uint64_t*)dp, pool_len, c->d_counter + 1, s));
   st = launch_score(c, (const uint64_t*)dp, pool_len, (const ps_req*)dr, n_req, (ps_result*)dout,
                     nullptr, nullptr, s);
   if (st != PS_OK) return st;
   HIP_TRY(c, hipMemcpyAsync(out, dout, (size_t)n_req * sizeof(ps_result), hipMemcpyDeviceToHost, s));
+  unsigned long long zero = ~0ull;
+  HIP_TRY(c, hipMemcpyAsync(&zero, c->d_counter + 1, sizeof zero, hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
-  return PS_OK;
+  return zero == ~0ull ? PS_OK : zero_hash(c, "pool", zero);
 }
 
 // After placements were committed on the device (work queued on `s`, the
@@ -1290,8 +1301,6 @@ ps_status ps_commit(ps_ctx* c, const uint64_t* pool, int64_t pool_len, const ps_
     if (s.P + add[(size_t)i] > PS_MAX_PENDING || s.S + add[(size_t)i] > PS_MAX_CONTEXT)
       return fail(c, PS_E_RANGE, "instance %d: token counters would exceed their limits", i);
   }
-  if (placed == 0) return PS_OK;
-
   DeviceScope ds(c->device);
   void *dp, *dr;
   if ((st = stage_buffer(c, 0, (size_t)pool_len * sizeof(uint64_t), &dp)) != PS_OK) return st;
@@ -1299,6 +1308,13 @@ ps_status ps_commit(ps_ctx* c, const uint64_t* pool, int64_t pool_len, const ps_
   hipStream_t s = c->stream;
   if (pool_len)
     HIP_TRY(c, hipMemcpyAsync(dp, pool, (size_t)pool_len * sizeof(uint64_t), hipMemcpyHostToDevice, s));
+  // no change before the pool is known to be free of zero hashes
+  HIP_TRY(c, ps_launch_first_zero((const uint64_t*)dp, pool_len, c->d_counter + 1, s));
+  unsigned long long zero = ~0ull;
+  HIP_TRY(c, hipMemcpyAsync(&zero, c->d_counter + 1, sizeof zero, hipMemcpyDeviceToHost, s));
+  HIP_TRY(c, hipStreamSynchronize(s));
+  if (zero != ~0ull) return zero_hash(c, "pool", zero);
+  if (placed == 0) return PS_OK;
   HIP_TRY(c, hipMemcpyAsync(dr, reqs, (size_t)n * sizeof(ps_req), hipMemcpyHostToDevice, s));
   HIP_TRY(c, hipMemsetAsync(c->d_counter, 0, sizeof(unsigned long long), s));
   std::vector<std::vector<uint32_t>> keep;

@@ -461,6 +461,8 @@ constexpr size_t kPoolIdleMax = (size_t)4 << 30;
 // Kernel launchers (ps_kernels.hip).
 hipError_t ps_launch_build(const ps::BuildArgs& a, hipStream_t s);  // slots, won, slot_of
 hipError_t ps_launch_rows(const ps::BuildArgs& a, hipStream_t s);   // rows, rowpos (needs rank)
+// Least index of a zero in v[0, n) into *at (~0: none); v 16-byte aligned.
+hipError_t ps_launch_first_zero(const uint64_t* v, int64_t n, unsigned long long* at, hipStream_t s);
 hipError_t ps_exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, ps::DevPool* pool,
                                  hipStream_t s);
 // fast: the policy of the four-requests-per-wave scorer (keyed selector,

@@ -42,7 +42,8 @@ __global__ void build_kernel(BuildArgs a) {
       else hi = mid;
     }
     uint32_t slot = 0;
-    const int r = insert_key(a.t, (uint32_t)lo, a.blk[k], &slot);
+    const uint64_t key = a.blk[k];
+    const int r = key != 0ull ? insert_key(a.t, (uint32_t)lo, key, &slot) : 0;
     // One counter update per wave when its lanes share the instance (a
     // list is contiguous), instead of one contended atomic per key.
     const int lane = threadIdx.x & 63;
@@ -77,6 +78,22 @@ __global__ void row_kernel(BuildArgs a) {
     a.t.rows[(size_t)lo * a.t.row_cap + pos] = a.blk[k];
     a.t.rowpos[(size_t)lo * a.t.slots + a.slot_of[k]] = pos;
   }
+}
+
+// Least index of a zero hash (~0: none), 16 bytes per lane and read.
+__global__ __launch_bounds__(256) void first_zero_kernel(const uint64_t* v, int64_t n, unsigned long long* at) {
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  unsigned long long first = ~0ull;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; 2 * k < n; k += stride) {
+    const int64_t i = 2 * k;
+    const bool pair = i + 1 < n;
+    const ulonglong2 x = pair ? reinterpret_cast<const ulonglong2*>(v)[k] : make_ulonglong2(v[i], 1ull);
+    if (x.x == 0ull || x.y == 0ull) {
+      first = (unsigned long long)(x.x == 0ull ? i : i + 1);
+      break;  // a thread's indices ascend
+    }
+  }
+  if (first != ~0ull) atomicMin(at, first);
 }
 
 // Hit of every request on every instance by direct probing, one wave per
@@ -2502,6 +2519,14 @@ size_t ps_score_lds_bytes(int32_t n_inst) {
 
 bool ps_hits_fit_lds(int32_t n_inst) {
   return (size_t)n_inst * sizeof(uint16_t) <= kLdsHitBudget;
+}
+
+hipError_t ps_launch_first_zero(const uint64_t* v, int64_t n, unsigned long long* at, hipStream_t s) {
+  hipError_t e = hipMemsetAsync(at, 0xFF, sizeof *at, s);
+  if (e != hipSuccess || n <= 0) return e;
+  const unsigned grid = (unsigned)((n + 4095) / 4096 < 4096 ? (n + 4095) / 4096 : 4096);
+  hipLaunchKernelGGL(first_zero_kernel, dim3(grid), dim3(256), 0, s, v, n, at);
+  return hipGetLastError();
 }
 
 hipError_t ps_launch_build(const BuildArgs& a, hipStream_t s) {

@@ -124,3 +124,30 @@ def test_commit_twice(ps, scorer):
     assert scorer.commit(w.pool, reqs_of(w), inst) == 0
     assert (scorer.state()["set_size"] == held).all()
     assert (scorer.state()["P"] == P).all()
+
+
+@pytest.mark.parametrize("at", [0, 1, 62, 4095, 4096, 12288, 12290])
+def test_zero_hash_refused(ps, scorer, at):
+    """A zero hash anywhere in a host pool or in the snapshot's lists: refused
+    with its index, nothing changed (odd and even lengths, first and last)."""
+    n = 12291
+    w = edge_window([[5, 6, 7], [8]], [list(range(10, 10 + n))], cap=2 * n)
+    load_window(scorer, w)
+    before = scorer.state()
+    pool = w.pool.copy()
+    pool[at] = 0
+    for call in (lambda: scorer.score(pool, reqs_of(w)),
+                 lambda: scorer.commit(pool, reqs_of(w), np.array([1], np.int32))):
+        with pytest.raises(ps.PackServeError, match=rf"zero block hash at pool\[{at}\]") as e:
+            call()
+        assert e.value.code == -1
+    blk = np.arange(1, n + 1, dtype=np.uint64)
+    blk[at] = 0
+    with pytest.raises(ps.PackServeError, match=rf"zero block hash at blk\[{at}\]"):
+        scorer.load(2, n, np.array([0, n // 2, n], np.int64), blk, w.D, w.Q, w.P, w.S, ps.make_model(
+            w.alpha, w.seg_ub, w.beta, w.gamma, 0.5, 0.05, 2.0, 556.0, 16, 512, 4_194_304))
+    after = scorer.state()
+    for k in before:
+        assert (before[k] == after[k]).all(), k
+    res = scorer.score(w.pool, reqs_of(w))  # the old snapshot still scores
+    compare_decisions(res, None, oracle.Oracle.from_window(w).window_score(w))
