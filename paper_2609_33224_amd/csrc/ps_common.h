@@ -544,6 +544,21 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // shifts, about three times as many).
 __device__ __forceinline__ float tok_f(int64_t x) { return (float)(double)x; }
 
+// Tokens of a number of blocks as fp32: both factors are exact (fewer than
+// 2^24 blocks, at most 1,024 tokens each), so the product is rounded once, as
+// the conversion of the exact count is, in one multiplication.
+template <class M>
+__device__ __forceinline__ float blocks_f(const M& m, int32_t blocks) {
+  return (float)blocks * (float)m.bs;
+}
+
+// A request's length in tokens and in blocks.
+struct ReqLen {
+  int64_t tokens;
+  int32_t blocks;
+  __device__ __forceinline__ operator int64_t() const { return tokens; }
+};
+
 // Eq. 7 with the empirical C and C^2 terms: n new, c cached tokens.
 template <class M>
 __device__ __forceinline__ float t_prefill(const M& m, float n, float c) {
@@ -569,7 +584,7 @@ struct Lat {
 template <class M>
 __device__ __forceinline__ float t_iter_of(const M& m, const InstState& st, int64_t L) {
   const auto& sg = m.seg[st.seg];
-  return sg[3] * (sg[0] + sg[1] * (float)st.A1 + sg[2] * (float)(st.S + L));
+  return sg[3] * (sg[0] + sg[1] * (float)st.A1 + sg[2] * tok_f(st.S + L));
 }
 
 template <class M>
@@ -580,7 +595,7 @@ __device__ __forceinline__ Lat latency(const M& m, const InstState& st, float n,
   const float interf = st.A1 > 1 ? tp / m.lout1 : 0.0f;
   Lat r;
   r.tpot = t_iter + interf;
-  r.ttft = tp + m.a[0] * (float)st.Q + m.a[1] * (float)st.P;
+  r.ttft = tp + m.a[0] * (float)st.Q + m.a[1] * tok_f(st.P);
   return r;
 }
 
@@ -593,6 +608,18 @@ __device__ __forceinline__ InstState shfl_state(const InstState& st, int src) {
   r.seg = __shfl(st.seg, src);
   r.P = __shfl(st.P, src);
   r.S = __shfl(st.S, src);
+  return r;
+}
+
+// The state in lane src (uniform: scalar registers).
+__device__ __forceinline__ InstState lane_state(const InstState& st, int src) {
+  InstState r;
+  r.D = __builtin_amdgcn_readlane(st.D, src);
+  r.Q = __builtin_amdgcn_readlane(st.Q, src);
+  r.A1 = __builtin_amdgcn_readlane(st.A1, src);
+  r.seg = __builtin_amdgcn_readlane(st.seg, src);
+  r.P = lane_value64(st.P, src);
+  r.S = lane_value64(st.S, src);
   return r;
 }
 
@@ -670,19 +697,19 @@ struct Member {
 // TTFT admission, so those branches compile away.
 template <bool KEYED = false, class M, class State>
 __device__ __forceinline__ Member member_with(const M& m, State state, uint32_t v,
-                                              int64_t L, float Lf, float wmin, float Z, bool kvc,
+                                              const ReqLen& L, float Lf, float wmin, float Z, bool kvc,
                                               float slo) {
   Member r{};
   const int64_t c_tok = (int64_t)v * m.bs;
   r.n_tok = L - c_tok;
-  const float n = (float)r.n_tok;
+  const float n = blocks_f(m, L.blocks - (int32_t)v);
   if (kvc) {
     const float W = fmaxf(0.0f, recompute_raw(m, n, Lf));
     if (!((W - wmin) / Z <= m.eta)) return r;
   }
   r.inC = true;
   r.st = state();
-  r.lt = latency(m, r.st, n, (float)c_tok, L);
+  r.lt = latency(m, r.st, n, blocks_f(m, (int32_t)v), L);
   const bool tpot_ok = (m.flags & PS_F_NO_TPOT_FILTER) || r.lt.tpot < m.tau;
   const bool ttft_ok = KEYED || !(m.flags & PS_F_TTFT_ADMIT) || r.lt.ttft <= slo;
   r.inT = tpot_ok && ttft_ok;
@@ -690,14 +717,14 @@ __device__ __forceinline__ Member member_with(const M& m, State state, uint32_t 
 }
 
 __device__ __forceinline__ Member member(const ScoreArgs& a, const DevModel& m, uint32_t i,
-                                         uint32_t v, int64_t L, float Lf, float wmin, float Z,
+                                         uint32_t v, const ReqLen& L, float Lf, float wmin, float Z,
                                          bool kvc, float slo) {
   return member_with(m, [&]() { return a.inst[i]; }, v, L, Lf, wmin, Z, kvc, slo);
 }
 
 template <bool KEYED = false, class M, class State>
 __device__ __forceinline__ void evaluate_with(const M& m, Acc& acc, uint32_t i, uint32_t v,
-                                              State state, int64_t L, float Lf, float wmin,
+                                              State state, const ReqLen& L, float Lf, float wmin,
                                               float Z, bool kvc, float slo) {
   const Member mb = member_with<KEYED>(m, state, v, L, Lf, wmin, Z, kvc, slo);
   if (!mb.inC) return;
@@ -721,7 +748,7 @@ __device__ __forceinline__ void evaluate_with(const M& m, Acc& acc, uint32_t i, 
 }
 
 __device__ __forceinline__ void evaluate(const ScoreArgs& a, const DevModel& m, Acc& acc,
-                                         uint32_t i, uint32_t v, int64_t L, float Lf, float wmin,
+                                         uint32_t i, uint32_t v, const ReqLen& L, float Lf, float wmin,
                                          float Z, bool kvc, float slo) {
   evaluate_with(m, acc, i, v, [&]() { return a.inst[i]; }, L, Lf, wmin, Z, kvc, slo);
 }

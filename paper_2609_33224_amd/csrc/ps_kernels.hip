@@ -277,10 +277,10 @@ __global__ __launch_bounds__(64) void lmax_kernel(const InstState* inst_key, con
     const int64_t room = st.A1 <= m.b_max ? m.kv_cap - st.S : -1;
     rm1 = room >= 0 ? (uint64_t)(room + 1) : 0ull;
     auto admits = [&](int32_t ell) {
-      const int64_t L = (int64_t)ell * m.bs;
+      const ReqLen L{(int64_t)ell * m.bs, ell};
       if (!eligible(m, st.A1, st.S, L)) return false;
       if (m.flags & PS_F_NO_TPOT_FILTER) return true;
-      return latency(m, st, (float)L, 0.0f, L).tpot < m.tau;
+      return latency(m, st, blocks_f(m, ell), 0.0f, L).tpot < m.tau;
     };
     if (admits(0)) {
       int32_t lo = 0, hi = PS_MAX_CHAIN + 1;  // admits(lo); hi fails or lies past the range
@@ -1356,8 +1356,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sc
       }
       const ChainRef c{a.pool + q.pre_off, a.pool + q.tail_off, q.pre_len, q.pre_len + q.tail_len};
       const int32_t ell = c.len;
-      const int64_t L = (int64_t)ell * m.bs;
-      const float Lf = (float)L;
+      const ReqLen L{(int64_t)ell * m.bs, ell};
+      const float Lf = blocks_f(m, L.blocks);
       // The group record (meta and up to 16 holders); a request with a
       // group result needs no staged chain.
       GroupMeta gm{0, kGroupNone};
@@ -1427,9 +1427,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sc
             const float Z = recompute_raw(m, Lf, Lf);
             const float W0 = fmaxf(0.0f, Z);
             const int64_t cK = (int64_t)hs * m.bs;
-            const float WK = fmaxf(0.0f, recompute_raw(m, (float)(L - cK), Lf));
+            const float WK = fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)hs), Lf));
             uint32_t wb = 0x7F800000u;
-            if (eel) wb = __float_as_uint(fmaxf(0.0f, recompute_raw(m, (float)(L - (int64_t)ehit * m.bs), Lf)));
+            if (eel) wb = __float_as_uint(fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)ehit), Lf)));
             if (lane == 0 && any0) wb = wb < __float_as_uint(W0) ? wb : __float_as_uint(W0);
             if (lane == 1 && anyK) wb = wb < __float_as_uint(WK) ? wb : __float_as_uint(WK);
             const float wmin = __uint_as_float(wave_min_u32(wb));
@@ -1440,7 +1440,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sc
             Acc acc{~0ull, ~0ull, ~0u, 0u, 0u};
             if (eel) evaluate_with<true>(m, acc, eid, ehit, [&]() { return est; }, L, Lf, wmin, Z, kvc, slo);
             if (admitK) {  // the class's first member of T in key order
-              const float nK = (float)(L - cK), cKf = (float)cK;
+              const float nK = blocks_f(m, L.blocks - (int32_t)hs), cKf = blocks_f(m, (int32_t)hs);
               // chunks of 64 key-ordered instances that may hold one: some
               // room holds L, and (monotone model: TPOT is at least t_iter
               // at L = 0, plus the class's interference when A1 > 1) some
@@ -1556,8 +1556,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sc
               const uint64_t em = __ballot(eact && eid == best);
               const uint32_t ev = (uint32_t)__shfl((int)ehit, em ? __builtin_ctzll(em) : 0);
               const uint32_t v = em ? ev : test_bit(hb, best) ? hs : 0u;
-              const int64_t c_tok = (int64_t)v * m.bs;
-              const Lat lt = latency(m, state_of(best), (float)(L - c_tok), (float)c_tok, L);
+              const Lat lt = latency(m, state_of(best), blocks_f(m, L.blocks - (int32_t)v), blocks_f(m, (int32_t)v), L);
               res = ps_result{(int32_t)best, (int32_t)v, lt.ttft, lt.tpot,
                               (t ? 0u : PS_R_FALLBACK) | (lt.ttft > slo ? PS_R_TTFT_MISS : 0u)};
               decided = true;
@@ -1719,7 +1718,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sc
       uint32_t wmin_bits = n0 > 0 ? __float_as_uint(W0) : 0x7F800000u;
       if (few) {
         if ((uint32_t)lane < nCand) {
-          const float W = fmaxf(0.0f, recompute_raw(m, (float)(L - (int64_t)myhit * m.bs), Lf));
+          const float W = fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)myhit), Lf));
           const uint32_t wb = __float_as_uint(W);
           wmin_bits = wb < wmin_bits ? wb : wmin_bits;
         }
@@ -1738,7 +1737,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sc
             if (lane == k) v = hk;
           }
           if (cand) {
-            const float W = fmaxf(0.0f, recompute_raw(m, (float)(L - (int64_t)v * m.bs), Lf));
+            const float W = fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)v), Lf));
             const uint32_t wb = __float_as_uint(W);
             wmin_bits = wb < wmin_bits ? wb : wmin_bits;
           }
@@ -1922,9 +1921,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sc
                       : run_walk<true>(a.t, best, c, stage, 0, g, s);
           }
         }
-        const int64_t c_tok = (int64_t)v * m.bs;
         const InstState st = state_of(best);
-        const Lat lt = latency(m, st, (float)(L - c_tok), (float)c_tok, L);
+        const Lat lt = latency(m, st, blocks_f(m, L.blocks - (int32_t)v), blocks_f(m, (int32_t)v), L);
         if (lt.ttft > slo) fl |= PS_R_TTFT_MISS;
         res = ps_result{(int32_t)best, (int32_t)v, lt.ttft, lt.tpot, fl};
       }
@@ -2028,33 +2026,33 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void le
         deferred_any = true;
         continue;
       }
-      const ChainRef c{a.pool + q.pre_off, a.pool + q.tail_off, q.pre_len, q.pre_len + q.tail_len};
-      const int32_t ell = c.len;
-      const int64_t L = (int64_t)ell * m.bs;
-      const float Lf = (float)L;
-      const int32_t p = q.pre_len;
+      // (uniform: one request per wave, so its chain sits in scalar registers)
+      const int32_t ell = (int32_t)uniform_u((uint32_t)(q.pre_len + q.tail_len));
+      const ChainRef c{a.pool + uniform64(q.pre_off), a.pool + uniform64(q.tail_off),
+                       (int32_t)uniform_u((uint32_t)q.pre_len), ell};
+      const ReqLen L{(int64_t)ell * m.bs, ell};
+      const float Lf = blocks_f(m, L.blocks);
+      const int32_t p = c.pre_len;
       uint32_t nA_exact = 0;
       if (a.sizes) nA_exact = (uint32_t)(n_inst - wave_lower_bound(a.room_sorted, n_inst, L, lane));
-      if (!(__shfl(trm.room, 0) >= L)) {  // A is empty: Reject
+      if (!(__ballot(trm.room >= L) & 1ull)) {  // A is empty: Reject
         if (lane == 0) {
           a.out[r] = ps_result{-1, 0, 0.0f, 0.0f, PS_R_REJECT};
           if (a.sizes) a.sizes[3 * (size_t)r] = a.sizes[3 * (size_t)r + 1] = a.sizes[3 * (size_t)r + 2] = 0;
         }
         continue;
       }
-      // The first chunk of zero-hit thresholds that admits this length, with
-      // the key-ordered states, read together with the holders' states.
+      // The first chunk of zero-hit thresholds that admits this length, read
+      // together with the holders' states.  (A chosen class member's state is
+      // read after the decision: keeping the chunk's states took the
+      // kernel past 128 registers, and 2 KB a request.)
       uint64_t cmask = fast0 ? __ballot(lane < n1 && lm1r >= ell) : 0ull;
       int32_t c0 = 0;
       int4 e = make_int4(-1, 0, 0, 0);
-      InstState est{};
       bool have = false;
       if (cmask) {
         const int32_t k = (int32_t)__builtin_ctzll(cmask) * 64 + lane;
-        if (k < n_inst) {
-          e = SMALL ? llm[k] : a.lm[k];
-          if (!SMALL) est = a.inst_key[k];
-        }
+        if (k < n_inst) e = SMALL ? llm[k] : a.lm[k];
         have = true;
       }
       // Holders: state (and with it eligibility) and hit; the holder bitmap.
@@ -2068,7 +2066,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void le
         el = eligible(m, hst.A1, hst.S, L);
         atomicOr(reinterpret_cast<unsigned long long*>(&bmH[id >> 6]), 1ull << (id & 63));
       }
-      if (SMALL && have && e.x >= 0) est = linst[e.y];
       __syncthreads();
       // Hits that reach the request's segment end continue on its tail.
       uint64_t need = __ballot(el && (int32_t)hit >= p);
@@ -2083,12 +2080,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void le
       // rooms: 64 eligible ones cannot all be among at most 16 holders).
       const bool topel = trm.room >= L;
       const bool any0 = __ballot(topel && !test_bit(bmH, (uint32_t)trm.id)) != 0ull ||
-                        __shfl(topel ? 1 : 0, 63) != 0;
+                        (__ballot(topel) >> 63) != 0ull;
       // Minimum recomputation penalty over A.
       const float Z = recompute_raw(m, Lf, Lf);  // T_pf(L, 0) - T_pf(0, L)
       const float W0 = fmaxf(0.0f, Z);
       uint32_t wb = 0x7F800000u;
-      if (el) wb = __float_as_uint(fmaxf(0.0f, recompute_raw(m, (float)(L - (int64_t)hit * m.bs), Lf)));
+      if (el) wb = __float_as_uint(fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)hit), Lf)));
       if (any0 && lane == 0) wb = wb < __float_as_uint(W0) ? wb : __float_as_uint(W0);
       const float wmin = __uint_as_float(wave_min_u32(wb));
       const float tpf_cold = t_prefill(m, Lf, 0.0f);
@@ -2098,15 +2095,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void le
       Acc acc{~0ull, ~0ull, ~0u, 0u, 0u};
       if (el) evaluate_with(m, acc, id, hit, [&]() { return hst; }, L, Lf, wmin, Z, kvc, slo);
       // The hit-0 class: eligible non-holders, one penalty W(L).
-      int32_t win0 = -1;  // lane of the class member found by the search
       if (admit0) {
         bool done0 = false;
         if (fast0) {
           while (have) {
             const uint64_t om = __ballot(e.x >= ell && !test_bit(bmH, (uint32_t)e.y));
             if (om) {
-              win0 = __builtin_ctzll(om);
-              if (lane == win0) {
+              if (lane == __builtin_ctzll(om)) {
                 InstState kst{};
                 kst.D = e.z;
                 kst.Q = e.w;
@@ -2128,10 +2123,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void le
             if (have) {
               const int32_t k = (c0 + (int32_t)__builtin_ctzll(cmask)) * 64 + lane;
               e = make_int4(-1, 0, 0, 0);
-              if (k < n_inst) {
-                e = SMALL ? llm[k] : a.lm[k];
-                est = SMALL ? linst[e.y] : a.inst_key[k];
-              }
+              if (k < n_inst) e = SMALL ? llm[k] : a.lm[k];
             }
           }
           // No member of the class is in T: its keys matter only for the
@@ -2161,21 +2153,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void le
       ps_result res{-1, 0, 0.0f, 0.0f, PS_R_REJECT};
       if (keyT != ~0ull || keyF != ~0ull) {
         const bool t = keyT != ~0ull;
-        const uint32_t best = (uint32_t)((t ? keyT : keyF) & 0xFFFFu);
+        const uint32_t best = uniform_u((uint32_t)(t ? keyT : keyF) & 0xFFFFu);
         const uint64_t hb = __ballot(el && id == best);
         InstState bs{};
         uint32_t v = 0;
         if (hb) {
           const int src = __builtin_ctzll(hb);
-          bs = shfl_state(hst, src);
-          v = (uint32_t)__shfl((int)hit, src);
-        } else if (win0 >= 0 && (uint32_t)__shfl(e.y, win0) == best) {
-          bs = shfl_state(est, win0);
+          bs = lane_state(hst, src);
+          v = (uint32_t)__builtin_amdgcn_readlane((int)hit, src);
         } else {
           bs = state_of(best);
         }
-        const int64_t c_tok = (int64_t)v * m.bs;
-        const Lat lt = latency(m, bs, (float)(L - c_tok), (float)c_tok, L);
+        const Lat lt = latency(m, bs, blocks_f(m, L.blocks - (int32_t)v), blocks_f(m, (int32_t)v), L);
         res = ps_result{(int32_t)best, (int32_t)v, lt.ttft, lt.tpot,
                         (t ? 0u : PS_R_FALLBACK) | (lt.ttft > slo ? PS_R_TTFT_MISS : 0u)};
       }
@@ -2315,8 +2304,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void le
     }
     const ChainRef c{a.pool + qd.pre_off, a.pool + qd.tail_off, qd.pre_len, qd.pre_len + qd.tail_len};
     const int32_t ell = c.len;
-    const int64_t L = (int64_t)ell * m.bs;
-    const float Lf = (float)L;
+    const ReqLen L{(int64_t)ell * m.bs, ell};
+    const float Lf = blocks_f(m, L.blocks);
     const int32_t p = qd.pre_len;
     // 0 scored here, 1 invalid, 2 left to the general kernel, 3 rejected
     uint32_t fate = !inr ? 4u : !valid ? 1u : (cnt == kGroupNone || (cnt & kGroupPop)) ? 2u
@@ -2385,7 +2374,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void le
     const float Z = recompute_raw(m, Lf, Lf);  // T_pf(L, 0) - T_pf(0, L)
     const float W0 = fmaxf(0.0f, Z);
     uint32_t wb = 0x7F800000u;
-    if (el) wb = __float_as_uint(fmaxf(0.0f, recompute_raw(m, (float)(L - (int64_t)hit * m.bs), Lf)));
+    if (el) wb = __float_as_uint(fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)hit), Lf)));
     if (any0 && t == 0) wb = wb < __float_as_uint(W0) ? wb : __float_as_uint(W0);
     const float wmin = __uint_as_float(row_min_u32(wb));
     const float tpf_cold = t_prefill(m, Lf, 0.0f);
@@ -2471,8 +2460,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void le
       const int src = (lane & 48) + (hb ? __builtin_ctz(hb) : 0);
       const uint32_t sv = (uint32_t)__shfl((int)hit, src);
       const uint32_t v = hb ? sv : 0u;
-      const int64_t c_tok = (int64_t)v * m.bs;
-      const Lat lt = latency(m, bs, (float)(L - c_tok), (float)c_tok, L);
+      const Lat lt = latency(m, bs, blocks_f(m, L.blocks - (int32_t)v), blocks_f(m, (int32_t)v), L);
       res = ps_result{(int32_t)best, (int32_t)v, lt.ttft, lt.tpot,
                       (tt ? 0u : PS_R_FALLBACK) | (lt.ttft > slo ? PS_R_TTFT_MISS : 0u)};
     }

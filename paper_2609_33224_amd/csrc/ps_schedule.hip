@@ -295,8 +295,8 @@ __global__ __launch_bounds__(kSeqMaxThreads) void spec_kernel(SchedArgs a) {
   const ps_req q = a.reqs[r];
   if (!req_valid(q, a.pool_len)) return;  // the scheduler rejects it without a look here
   const DevModel& m = *a.model;
-  const int64_t L = ((int64_t)q.pre_len + q.tail_len) * m.bs;
-  const float Lf = (float)L;
+  const ReqLen L{((int64_t)q.pre_len + q.tail_len) * m.bs, q.pre_len + q.tail_len};
+  const float Lf = blocks_f(m, L.blocks);
   const float Z = recompute_raw(m, Lf, Lf);
   const float slo = fmaxf(m.ttft_floor, t_prefill(m, Lf, 0.0f));
   const bool kvc = !(m.flags & PS_F_NO_KVC_FILTER) && Z > 0.0f;
@@ -321,7 +321,7 @@ __global__ __launch_bounds__(kSeqMaxThreads) void spec_kernel(SchedArgs a) {
       if (base + u * NT + tid >= n_inst || !eligible(m, st[u].A1, st[u].S, L)) continue;
       ++al;
       const uint32_t wb =
-          __float_as_uint(fmaxf(0.0f, recompute_raw(m, (float)(L - (int64_t)hv[u] * m.bs), Lf)));
+          __float_as_uint(fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)hv[u]), Lf)));
       wl = wb < wl ? wb : wl;
     }
   }
@@ -671,8 +671,8 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
     const uint32_t wmin_b = uniform_u(in.head[3]);
     const bool valid = len != ~0u;
     const int32_t ell = valid ? (int32_t)len : 0;
-    const int64_t L = (int64_t)ell * m.bs;
-    const float Lf = tok_f(L);
+    const ReqLen L{(int64_t)ell * m.bs, ell};
+    const float Lf = blocks_f(m, L.blocks);
     int32_t best = -1;
     uint32_t fl = valid ? PS_R_REJECT : PS_R_INVALID, nA = 0, nC = 0, nT = 0;
     bool outside = false;  // the choice is not a changed instance
@@ -699,7 +699,7 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
           hx_my = lm > h_my ? lm : h_my;
           eb = eligible(m, so.A1, so.S, L);
           ec = eligible(m, sc.A1, sc.S, L);
-          wb = __float_as_uint(fmaxf(0.0f, recompute_raw(m, tok_f(L - (int64_t)h_my * m.bs), Lf)));
+          wb = __float_as_uint(fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)h_my), Lf)));
           if (want_sizes && eb) {
             const Member mb = member_with(m, [&]() { return so; }, h_my, L, Lf, wmin, Z, kvc, slo);
             cb = mb.inC;
@@ -816,7 +816,7 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
           if (!eligible(m, st.A1, st.S, L)) continue;
           ++al;
           const uint32_t wb =
-              __float_as_uint(fmaxf(0.0f, recompute_raw(m, tok_f(L - (int64_t)hit_of((uint32_t)i) * m.bs), Lf)));
+              __float_as_uint(fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)hit_of((uint32_t)i)), Lf)));
           wl = wb < wl ? wb : wl;
         }
         al = wave_sum_u32(al);
@@ -939,11 +939,10 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
     if (best < 0) {
       a.out[r] = ps_result{-1, 0, 0.0f, 0.0f, fl};
     } else {
-      const int64_t L = (int64_t)sh.blen[t] * m.bs;
-      const int64_t c_tok = (int64_t)sh.hit[t] * m.bs;
+      const ReqLen L{(int64_t)sh.blen[t] * m.bs, (int32_t)sh.blen[t]};
       const InstState st = sh.st[t];
-      const Lat lt = latency(m, st, (float)(L - c_tok), (float)c_tok, L);
-      if (lt.ttft > fmaxf(m.ttft_floor, t_prefill(m, (float)L, 0.0f))) fl |= PS_R_TTFT_MISS;
+      const Lat lt = latency(m, st, blocks_f(m, L.blocks - (int32_t)sh.hit[t]), blocks_f(m, (int32_t)sh.hit[t]), L);
+      if (lt.ttft > fmaxf(m.ttft_floor, t_prefill(m, blocks_f(m, L.blocks), 0.0f))) fl |= PS_R_TTFT_MISS;
       a.out[r] = ps_result{best, (int32_t)sh.hit[t], lt.ttft, lt.tpot, fl};
     }
     if (a.sizes) {

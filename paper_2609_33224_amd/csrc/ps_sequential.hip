@@ -230,8 +230,8 @@ __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
     if (tid == 0) sh.n_scored += 1u;
     const ChainRef c{a.pool + q.pre_off, a.pool + q.tail_off, q.pre_len, q.pre_len + q.tail_len};
     const int32_t ell = c.len;
-    const int64_t L = (int64_t)ell * m.bs;
-    const float Lf = (float)L;
+    const ReqLen L{(int64_t)ell * m.bs, ell};
+    const float Lf = blocks_f(m, L.blocks);
     uint32_t* H = a.hits + (size_t)(r - a.r0) * (size_t)n_inst;
     const int32_t forced = replay ? a.forced[r] : -1;
 
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
 #pragma unroll
           for (int u = 0; u < kSeqB; ++u) {
             if (base + u * NT + tid >= n_inst || !eligible(m, st[u].A1, st[u].S, L)) continue;
-            const float W = fmaxf(0.0f, recompute_raw(m, (float)(L - (int64_t)hv[u] * m.bs), Lf));
+            const float W = fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)hv[u]), Lf));
             const uint32_t wb = __float_as_uint(W);
             wl = wb < wl ? wb : wl;
           }
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
       const uint32_t v = H[best];
       const int64_t c_tok = (int64_t)v * m.bs;
       InstState st = a.inst[best];
-      const Lat lt = latency(m, st, (float)(L - c_tok), (float)c_tok, L);
+      const Lat lt = latency(m, st, blocks_f(m, L.blocks - (int32_t)v), blocks_f(m, (int32_t)v), L);
       if (lt.ttft > slo) fl |= PS_R_TTFT_MISS;
       a.out[r] = ps_result{best, (int32_t)v, lt.ttft, lt.tpot, fl};
       if (a.sizes) {
