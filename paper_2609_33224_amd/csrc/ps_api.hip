@@ -119,6 +119,7 @@ struct ps_ctx {
   uint32_t* d_order0 = nullptr;
   InstState* d_inst_key = nullptr;  // states in d_order0's order
   TopRoom* d_rtop = nullptr;         // the kTopRooms largest rooms with their ids
+  uint32_t* d_rank = nullptr;        // ranks of the derivation (2 per instance)
   int32_t lean_wpc = 0;              // resident lean-scorer waves per CU (0: not asked yet)
   int32_t rows_wpc = 0;              // the same for the four-requests-per-wave scorer
   int32_t score_wpc = 0;             // the same for the general scorer (fast policy)
@@ -348,7 +349,7 @@ ps_status zero_hash(ps_ctx* c, const char* what, unsigned long long at) {
 
 void free_snapshot(ps_ctx* c) {
   c->pool.put(c->t.keys, c->t.count, c->t.rows, c->t.rowpos, c->d_inst, c->d_room, c->d_room_sorted,
-              c->d_order0, c->d_inst_key, c->d_rtop, c->d_lm, c->d_lm1, c->d_csum, c->d_scratch);
+              c->d_order0, c->d_inst_key, c->d_rtop, c->d_rank, c->d_lm, c->d_lm1, c->d_csum, c->d_scratch);
   ps_free_index(&c->x, &c->pool);
   c->loaded = false;
 }
@@ -362,72 +363,28 @@ ps_status refresh_lmax(ps_ctx* c) {
   return PS_OK;
 }
 
-// The kTopRooms largest rooms with their ids, descending (pads: room -1).
-std::vector<TopRoom> top_rooms(const std::vector<int64_t>& room) {
-  std::vector<TopRoom> t(room.size());
-  for (size_t i = 0; i < room.size(); ++i) t[i] = TopRoom{room[i], (int32_t)i, 0};
-  const size_t k = std::min(room.size(), (size_t)kTopRooms);
-  std::partial_sort(t.begin(), t.begin() + (long)k, t.end(),
-                    [](const TopRoom& x, const TopRoom& y) { return x.room > y.room; });
-  t.resize(kTopRooms, TopRoom{-1, 0, 0});
-  return t;
-}
-
-// Per-instance room (kv_cap - S when A + 1 <= B_max, else -1; an instance
-// is capacity-eligible for a request of L tokens iff L <= room) and the same
-// values sorted ascending, so |A| is one binary search.
-std::vector<int64_t> rooms_of(const std::vector<InstState>& hs, const DevModel& m) {
-  std::vector<int64_t> r(hs.size());
-  for (size_t i = 0; i < hs.size(); ++i) r[i] = hs[i].A1 <= m.b_max ? m.kv_cap - hs[i].S : -1;
-  return r;
-}
-
 int32_t segment_of_dev(const DevModel& m, int32_t B) {
   for (int32_t s = 0; s < m.n_seg; ++s)
     if (B <= m.seg_ub[s]) return s;
   return m.n_seg - 1;
 }
 
-// Instance ids in the order of the packing key of a candidate with no cached
-// prefix: most decoding first, then fewest queued, then lowest id.
-std::vector<InstState> states_in_order(const std::vector<InstState>& hs,
-                                       const std::vector<uint32_t>& order) {
-  std::vector<InstState> v(order.size());
-  for (size_t k = 0; k < order.size(); ++k) v[k] = hs[order[k]];
-  return v;
+DeriveArgs derive_args(const ps_ctx& c, int32_t n, const DevModel& m) {
+  return DeriveArgs{c.d_inst, n, m.b_max, m.kv_cap, c.d_room, c.d_room_sorted, c.d_order0, c.d_inst_key, c.d_rtop,
+                    c.d_rank};
 }
 
-std::vector<uint32_t> key_order(const std::vector<InstState>& hs) {
-  std::vector<uint32_t> o(hs.size());
-  for (size_t i = 0; i < o.size(); ++i) o[i] = (uint32_t)i;
-  std::sort(o.begin(), o.end(), [&](uint32_t x, uint32_t y) {
-    if (hs[x].D != hs[y].D) return hs[x].D > hs[y].D;
-    if (hs[x].Q != hs[y].Q) return hs[x].Q < hs[y].Q;
-    return x < y;
-  });
-  return o;
-}
-
-// Upload the host copy of the instance state and everything derived from it
-// (rooms, sorted rooms, key order).
+// Upload the host copy of the instance state and derive what follows from it.
+// (The copy waits for work on the default stream, as a scoring call there may
+// still read what is derived here.)
 ps_status refresh_derived(ps_ctx* c) {
   for (InstState& st : c->h_state) {
     st.A1 = st.D + st.Q + 1;
     st.seg = segment_of_dev(c->h_model, st.A1);
   }
-  const std::vector<int64_t> room = rooms_of(c->h_state, c->h_model);
-  std::vector<int64_t> rs = room;
-  std::sort(rs.begin(), rs.end());
-  const std::vector<uint32_t> o0 = key_order(c->h_state);
   HIP_TRY(c, hipMemcpy(c->d_inst, c->h_state.data(), c->h_state.size() * sizeof(InstState),
                        hipMemcpyHostToDevice));
-  HIP_TRY(c, hipMemcpy(c->d_room, room.data(), room.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-  HIP_TRY(c, hipMemcpy(c->d_room_sorted, rs.data(), rs.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-  const std::vector<TopRoom> tr = top_rooms(room);
-  HIP_TRY(c, hipMemcpy(c->d_rtop, tr.data(), tr.size() * sizeof(TopRoom), hipMemcpyHostToDevice));
-  HIP_TRY(c, hipMemcpy(c->d_order0, o0.data(), o0.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-  const std::vector<InstState> ik = states_in_order(c->h_state, o0);
-  HIP_TRY(c, hipMemcpy(c->d_inst_key, ik.data(), ik.size() * sizeof(InstState), hipMemcpyHostToDevice));
+  HIP_TRY(c, ps_launch_derive(derive_args(*c, c->n_inst, c->h_model), c->stream));
   return refresh_lmax(c);
 }
 
@@ -582,7 +539,7 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
   auto cleanup = [&]() {
     free_build_temps();
     c->pool.put(fresh.t.keys, fresh.t.count, fresh.t.rows, fresh.t.rowpos, fresh.d_inst, fresh.d_room,
-                fresh.d_room_sorted, fresh.d_order0, fresh.d_inst_key, fresh.d_rtop, fresh.d_lm,
+                fresh.d_room_sorted, fresh.d_order0, fresh.d_inst_key, fresh.d_rtop, fresh.d_rank, fresh.d_lm,
                 fresh.d_lm1, fresh.d_csum, fresh.d_scratch);
     ps_free_index(&fresh.x, &c->pool);
   };
@@ -601,6 +558,7 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
   if (e == hipSuccess) e = c->pool.get(&fresh.d_order0, (size_t)n * sizeof(uint32_t));
   if (e == hipSuccess) e = c->pool.get(&fresh.d_inst_key, (size_t)n * sizeof(InstState));
   if (e == hipSuccess) e = c->pool.get(&fresh.d_rtop, (size_t)kTopRooms * sizeof(TopRoom));
+  if (e == hipSuccess) e = c->pool.get(&fresh.d_rank, 2 * (size_t)n * sizeof(uint32_t));
   if (e == hipSuccess) e = c->pool.get(&fresh.d_lm, (size_t)n * sizeof(int4));
   if (e == hipSuccess) e = c->pool.get(&fresh.d_lm1, (size_t)((n + 63) / 64) * sizeof(int32_t));
   if (e == hipSuccess) e = c->pool.get(&fresh.d_csum, (size_t)((n + 63) / 64) * sizeof(uint4));
@@ -624,11 +582,6 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
     s.S = in->ctx_tok[i];
   }
   const DevModel dm = device_model(*m);
-  const std::vector<int64_t> hroom = rooms_of(hs, dm);
-  std::vector<int64_t> hroom_sorted = hroom;
-  std::sort(hroom_sorted.begin(), hroom_sorted.end());
-  const std::vector<uint32_t> horder0 = key_order(hs);
-  const std::vector<InstState> hinst_key = states_in_order(hs, horder0);
   hipStream_t sm = c->stream;
   e = hipMemsetAsync(fresh.t.keys, 0, tab_bytes, sm);
   if (e == hipSuccess) e = hipMemsetAsync(fresh.t.count, 0, (size_t)n * sizeof(uint32_t), sm);
@@ -639,21 +592,7 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
     e = hipMemcpyAsync(d_blk, in->blk, (size_t)n_blk * sizeof(uint64_t), hipMemcpyHostToDevice, sm);
   if (e == hipSuccess)
     e = hipMemcpyAsync(fresh.d_inst, hs.data(), hs.size() * sizeof(InstState), hipMemcpyHostToDevice, sm);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(fresh.d_room, hroom.data(), hroom.size() * sizeof(int64_t), hipMemcpyHostToDevice, sm);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(fresh.d_room_sorted, hroom_sorted.data(), hroom_sorted.size() * sizeof(int64_t),
-                       hipMemcpyHostToDevice, sm);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(fresh.d_order0, horder0.data(), horder0.size() * sizeof(uint32_t),
-                       hipMemcpyHostToDevice, sm);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(fresh.d_inst_key, hinst_key.data(), hinst_key.size() * sizeof(InstState),
-                       hipMemcpyHostToDevice, sm);
-  const std::vector<TopRoom> htop = top_rooms(hroom);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(fresh.d_rtop, htop.data(), htop.size() * sizeof(TopRoom), hipMemcpyHostToDevice,
-                       sm);
+  if (e == hipSuccess) e = ps_launch_derive(derive_args(fresh, n, dm), sm);
   BuildArgs ba{fresh.t, d_off, d_blk, n, n_blk, c->d_counter, d_won, d_slot, d_rank};
   // zero hashes are looked for on the device, beside the build, which skips
   // them (6 M hashes take one host thread 2 ms)
@@ -699,6 +638,7 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
   c->d_order0 = fresh.d_order0;
   c->d_inst_key = fresh.d_inst_key;
   c->d_rtop = fresh.d_rtop;
+  c->d_rank = fresh.d_rank;
   c->lean_wpc = 0;
   c->rows_wpc = 0;
   c->score_wpc = 0;
@@ -730,6 +670,7 @@ ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m
   fresh.d_order0 = nullptr;
   fresh.d_inst_key = nullptr;
   fresh.d_rtop = nullptr;
+  fresh.d_rank = nullptr;
   fresh.d_lm = nullptr;
   fresh.d_lm1 = nullptr;
   fresh.d_csum = nullptr;
@@ -1171,21 +1112,13 @@ ps_status ps_score_window(ps_ctx* c, const uint64_t* pool, int64_t pool_len, con
 // index).  Synchronous.
 static ps_status after_commit(ps_ctx* c, hipStream_t s, int64_t* n_dropped) {
   unsigned long long dropped = 0;
+  HIP_TRY(c, ps_launch_derive(derive_args(*c, c->n_inst, c->h_model), s));
   HIP_TRY(c, hipMemcpyAsync(&dropped, c->d_counter, sizeof dropped, hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipMemcpyAsync(c->h_state.data(), c->d_inst, c->h_state.size() * sizeof(InstState),
                             hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipMemcpyAsync(c->h_count.data(), c->t.count, c->h_count.size() * sizeof(uint32_t),
                             hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
-  std::vector<int64_t> rs = rooms_of(c->h_state, c->h_model);
-  const std::vector<TopRoom> tr = top_rooms(rs);
-  HIP_TRY(c, hipMemcpy(c->d_rtop, tr.data(), tr.size() * sizeof(TopRoom), hipMemcpyHostToDevice));
-  std::sort(rs.begin(), rs.end());
-  HIP_TRY(c, hipMemcpy(c->d_room_sorted, rs.data(), rs.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-  const std::vector<uint32_t> o0 = key_order(c->h_state);
-  HIP_TRY(c, hipMemcpy(c->d_order0, o0.data(), o0.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-  const std::vector<InstState> ik = states_in_order(c->h_state, o0);
-  HIP_TRY(c, hipMemcpy(c->d_inst_key, ik.data(), ik.size() * sizeof(InstState), hipMemcpyHostToDevice));
   HIP_TRY(c, ps_build_index(c->t, c->n_inst, c->h_count.data(), &c->x, &c->pool, s));
   HIP_TRY(c, hipStreamSynchronize(s));
   const ps_status lst = refresh_lmax(c);

@@ -405,6 +405,18 @@ struct SchedArgs {
   int32_t* grp_inst;
 };
 
+struct DeriveArgs {
+  const InstState* inst;
+  int32_t n, b_max;
+  int64_t kv_cap;
+  int64_t* room;
+  int64_t* room_sorted;
+  uint32_t* order0;
+  InstState* inst_key;
+  TopRoom* rtop;
+  uint32_t* rank;  // 2 n: in the key order, among the rooms
+};
+
 struct BuildArgs {
   Tables t;
   const int64_t* blk_off;
@@ -497,6 +509,8 @@ void ps_free_index(ps::GIndex* x, ps::DevPool* pool);
 hipError_t ps_launch_commit(const ps::CommitBatch& b, uint32_t max_grp, uint32_t max_pos, hipStream_t s);
 size_t ps_commit_ws_bytes(uint32_t n_ent, uint32_t n_grp, uint32_t n_pos);
 void ps_commit_ws_bind(ps::CommitBatch* b, void* ws, uint32_t n_ent, uint32_t n_grp, uint32_t n_pos);
+// Rooms, sorted rooms, largest rooms and key order from the states.
+hipError_t ps_launch_derive(const ps::DeriveArgs& a, hipStream_t s);
 // Zero-hit admission thresholds in key order and their chunk maxima.
 hipError_t ps_launch_lmax(const ps::InstState* inst_key, const uint32_t* order0,
                           const ps::DevModel* m, int32_t n, int4* lm, int32_t* lm1, uint4* csum,

@@ -96,6 +96,75 @@ __global__ __launch_bounds__(256) void first_zero_kernel(const uint64_t* v, int6
   if (first != ~0ull) atomicMin(at, first);
 }
 
+// What the scorers read about the pool beside the states: the rooms, the
+// rooms sorted, the largest ones, and ids and states in the order of the
+// packing key of a candidate with no cached prefix (most decoding, fewest
+// queued, lowest id).  Sorted by rank: every instance counts the instances
+// before it, a tile of them per workgroup, so that the sort is as wide as the
+// chip (16 M comparisons at 4,096 instances, 5 us).  Sorting on the host and
+// uploading five arrays, one synchronous copy of about 30 us each, took 100 us
+// at 64 instances and 210 us at 1,024.
+constexpr int kRankTile = 256;
+
+__device__ __forceinline__ uint64_t key0_of(const InstState& st, uint32_t i) {
+  return (uint64_t)(PS_MAX_DQ - st.D) << 32 | (uint64_t)st.Q << 16 | i;
+}
+
+__global__ __launch_bounds__(kRankTile) void rooms_kernel(DeriveArgs a) {
+  const int32_t i = blockIdx.x * kRankTile + threadIdx.x;
+  if (i < a.n) {
+    const InstState st = a.inst[i];
+    // (an instance is capacity-eligible for L tokens iff L <= room)
+    a.room[i] = st.A1 <= a.b_max ? a.kv_cap - st.S : -1;
+    a.rank[i] = a.rank[(size_t)a.n + i] = 0u;
+  }
+  // pads of the largest rooms (pools smaller than the list)
+  if (i < kTopRooms && i >= a.n) a.rtop[i] = TopRoom{-1, 0, 0};
+}
+
+__global__ __launch_bounds__(kRankTile) void rank_kernel(DeriveArgs a) {
+  __shared__ uint64_t key[kRankTile];
+  __shared__ int64_t room[kRankTile];
+  const int32_t i = blockIdx.x * kRankTile + threadIdx.x;
+  uint64_t ki = 0ull;
+  int64_t ri = 0;
+  if (i < a.n) {
+    ki = key0_of(a.inst[i], (uint32_t)i);
+    ri = a.room[i];
+  }
+  uint32_t nk = 0u, nr = 0u;
+  for (int32_t j0 = (int32_t)blockIdx.y * kRankTile; j0 < a.n; j0 += (int32_t)gridDim.y * kRankTile) {
+    const int32_t j = j0 + (int32_t)threadIdx.x;
+    __syncthreads();
+    if (j < a.n) {
+      key[threadIdx.x] = key0_of(a.inst[j], (uint32_t)j);
+      room[threadIdx.x] = a.room[j];
+    }
+    __syncthreads();
+    const int32_t nj = a.n - j0 < kRankTile ? a.n - j0 : kRankTile;
+    for (int32_t t = 0; t < nj; ++t) {
+      nk += key[t] < ki ? 1u : 0u;
+      nr += room[t] < ri || (room[t] == ri && j0 + t < i) ? 1u : 0u;
+    }
+  }
+  if (i < a.n) {
+    if (nk) atomicAdd(&a.rank[i], nk);
+    if (nr) atomicAdd(&a.rank[(size_t)a.n + i], nr);
+  }
+}
+
+__global__ __launch_bounds__(kRankTile) void order_kernel(DeriveArgs a) {
+  const int32_t i = blockIdx.x * kRankTile + threadIdx.x;
+  if (i >= a.n) return;
+  const uint32_t k = a.rank[i], r = a.rank[(size_t)a.n + i];
+  const int64_t room = a.room[i];
+  a.order0[k] = (uint32_t)i;
+  a.inst_key[k] = a.inst[i];
+  a.room_sorted[r] = room;
+  const uint32_t top = (uint32_t)a.n - 1u - r;
+  if (top < (uint32_t)kTopRooms) a.rtop[top] = TopRoom{room, i, 0};
+}
+
 // Hit of every request on every instance by direct probing, one wave per
 // request.  Lane l probes the first block on instance base + 64 r + l (BR x
 // 64 instances per step, a whole 64-byte bucket per lane), then each
@@ -2641,6 +2710,17 @@ int32_t ps_score_waves_per_cu(int32_t n_inst, bool hits_in_lds, bool fast) {
     e = fast ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, score_kernel<false, false, true>, 64, lds)
              : hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, score_kernel<false, false, false>, 64, lds);
   return e == hipSuccess && blocks > 0 ? blocks : 12;
+}
+
+hipError_t ps_launch_derive(const DeriveArgs& a, hipStream_t s) {
+  if (a.n <= 0) return hipSuccess;
+  const unsigned tiles = (unsigned)((a.n + kRankTile - 1) / kRankTile);
+  const unsigned pads = (unsigned)((kTopRooms + kRankTile - 1) / kRankTile);
+  hipLaunchKernelGGL(rooms_kernel, dim3(tiles > pads ? tiles : pads), dim3(kRankTile), 0, s, a);
+  // at most 16 tiles' sums per instance: an atomic each
+  hipLaunchKernelGGL(rank_kernel, dim3(tiles, tiles < 16u ? tiles : 16u), dim3(kRankTile), 0, s, a);
+  hipLaunchKernelGGL(order_kernel, dim3(tiles), dim3(kRankTile), 0, s, a);
+  return hipGetLastError();
 }
 
 hipError_t ps_launch_lmax(const InstState* inst_key, const uint32_t* order0, const DevModel* m,
