@@ -361,16 +361,23 @@ __global__ __launch_bounds__(kCommitThreads) void commit_drop_kernel(CommitBatch
     for (int u = 0; u < kCommitU; ++u) {
       const uint32_t p = p0 + u * kCommitThreads + threadIdx.x;
       bool refused = false;
+      uint32_t ent = 0u, at = 0u;
       if (p < h.n_pos) {
         const uint32_t s = b.pos_slot[p];
         if (s < kPosZero) {
           const uint32_t e = entry_of(b, h.n_ent, ce, lds, p);
           refused = b.grp_count[b.ent_grp[e]] + (uint32_t)b.set_key[s] >= b.cap;
           const uint32_t j = p - b.ent_off[e];
-          if (refused && j < b.ent_hit[e]) atomicMin(&b.ent_hit[e], j);
+          ent = e;
+          at = j;
         }
       }
-      n += (unsigned long long)__popcll(__ballot(refused));
+      const uint64_t rm = __ballot(refused);
+      n += (unsigned long long)__popcll(rm);
+      // (one atomic per wave and entry: positions ascend with the lanes)
+      const uint32_t e_prev = (uint32_t)__shfl_up((int)ent, 1);
+      const bool first = refused && (lane == 0 || !((rm >> (lane - 1)) & 1ull) || e_prev != ent);
+      if (first && at < b.ent_hit[ent]) atomicMin(&b.ent_hit[ent], at);
     }
   }
   if (lane == 0 && n) atomicAdd(b.dropped, n);
