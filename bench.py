@@ -756,8 +756,8 @@ def sequential_block(sc, win, model, d_pool, d_reqs, n, snap, reps, stream):
     return {
         "entry": "ps_schedule_window_dev: Algorithm 1 per arrival (batches of 256: hits pass, "
                  "every request scored in parallel against the batch's starting state, then "
-                 "one workgroup checks each result against the instances placed on since, "
-                 "decides and commits in arrival order; rebuild of the derived data)",
+                 "one workgroup decides in arrival order from that and the instances placed on "
+                 "since; the batch's blocks committed together; rebuild of the derived data)",
         "requests": n, "of_window": win.n_req,
         "ms_per_call": ms, "decisions_per_s": n / (ms * 1e-3),
         "us_per_decision": ms * 1e3 / n, "reps": reps,

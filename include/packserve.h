@@ -295,9 +295,10 @@ ps_status ps_schedule_window_dev(ps_ctx* ctx, const uint64_t* d_pool, int64_t po
 
 /*
  * Device memory the two calls above may hold for the hits of the requests
- * one launch schedules (n_inst x 4 bytes per request): a window whose hits
- * exceed it is scheduled in several launches, in order, with identical
- * results.  0 restores the default, 256 MiB; any budget admits at least one
+ * one launch schedules (n_inst x 4 bytes per request; the batches of
+ * ps_schedule_window_dev, 256 requests at most, hold a list of the walks of
+ * the same size beside them): a window whose hits exceed it is scheduled in
+ * several launches, in order, with identical results.  0 restores the default, 256 MiB; any budget admits at least one
  * request per launch.  The memory is kept by the context until ps_destroy.
  */
 ps_status ps_set_schedule_budget(ps_ctx* ctx, int64_t bytes);
@@ -306,13 +307,13 @@ ps_status ps_set_schedule_budget(ps_ctx* ctx, int64_t bytes);
  * Speculative batches of ps_schedule_window_dev (Algorithm 1 per request,
  * Sec. 6, with the state moving along the request path, Sec. 7, as above;
  * the results do not depend on this setting).  The requests are taken in
- * batches of `batch`: every request of a batch is first scored in parallel
- * against the state at the batch's start, keeping |A|, |C|, |T|, W_min and
- * the first members of T and of C in key order; then, in arrival order, the
- * instances that earlier requests of the batch were placed on are scored
- * again against the current state, and when they cannot change W_min and
- * the speculative lists show the least key, the request is decided from
- * them; otherwise it is scored in full.  batch in [1, 256]; 0 scores every
+ * batches of at most `batch`: every request of a batch is first scored in
+ * parallel against the state at the batch's start, keeping |A|, |C|, |T|,
+ * W_min and the first members of T and of C in key order; then, in arrival
+ * order, the instances that earlier requests of the batch were placed on
+ * are scored again against the current state, and when they cannot change
+ * W_min and the speculative lists show the least key, the request is decided
+ * from them; otherwise it is scored in full.  batch in [1, 256]; 0 scores every
  * request in full (one workgroup, no speculation).  Default 256.  The
  * Random and H-C-Q selectors are always scored in full.  PS_E_INVAL for a
  * batch outside [0, 256].
