@@ -107,7 +107,7 @@ struct ps_ctx {
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   int num_cus = 0;
   std::string err;
-  DevPool pool;  // snapshot, index and build buffers
+  DevPool pool;  // all device memory of the context
   bool loaded = false;
   // snapshot
   int32_t n_inst = 0;
@@ -221,20 +221,13 @@ struct DeviceScope {
   }
 };
 
-template <class T>
-void dfree(T*& p) {
-  if (p) (void)hipFree((void*)p);
-  p = nullptr;
-}
-
 // Grows staging buffer k to at least `bytes`.
 ps_status stage_buffer(ps_ctx* c, int k, size_t bytes, void** out) {
   if (bytes > c->stage_cap[k]) {
-    if (c->d_stage[k]) (void)hipFree(c->d_stage[k]);
-    c->d_stage[k] = nullptr;
+    c->pool.release(c->d_stage[k]);
     c->stage_cap[k] = 0;
     size_t want = std::max(bytes, (size_t)4096);
-    HIP_TRY(c, hipMalloc(&c->d_stage[k], want));
+    HIP_TRY(c, c->pool.grow(&c->d_stage[k], want));
     c->stage_cap[k] = want;
   }
   *out = c->d_stage[k];
@@ -410,6 +403,7 @@ ps_status ps_create(int device, ps_ctx** out) {
   ps_ctx* c = new (std::nothrow) ps_ctx();
   if (!c) return fail(nullptr, PS_E_NOMEM, "host allocation failed");
   c->device = device;
+  c->pool.set_device(device);
   DeviceScope ds(device);
   hipDeviceProp_t prop;
   e = hipGetDeviceProperties(&prop, device);
@@ -417,8 +411,8 @@ ps_status ps_create(int device, ps_ctx** out) {
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->fork_ev, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->join_ev, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipMalloc((void**)&c->d_model, sizeof(DevModel));
-  if (e == hipSuccess) e = hipMalloc((void**)&c->d_counter, 2 * sizeof(unsigned long long));
+  if (e == hipSuccess) e = c->pool.grow(&c->d_model, sizeof(DevModel));
+  if (e == hipSuccess) e = c->pool.grow(&c->d_counter, 2 * sizeof(unsigned long long));
   if (e != hipSuccess) {
     ps_destroy(c);
     return fail(nullptr, PS_E_DEVICE, "device set-up failed: %s", hipGetErrorString(e));
@@ -450,24 +444,23 @@ ps_status ps_destroy(ps_ctx* c) {
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   if (c->aux) (void)hipStreamSynchronize(c->aux);
   free_snapshot(c);
-  dfree(c->d_model);
-  dfree(c->d_counter);
-  for (int k = 0; k < 4; ++k)
-    if (c->d_stage[k]) (void)hipFree(c->d_stage[k]);
-  dfree(c->d_seq_hits);
-  dfree(c->d_seq_stats);
-  dfree(c->d_gkeys);
-  dfree(c->d_grec);
-  dfree(c->d_gslot);
-  dfree(c->d_dcnt);
-  dfree(c->d_dlist);
-  dfree(c->d_gpop);
-  dfree(c->d_glist);
-  dfree(c->d_gplist);
-  dfree(c->d_grep);
-  dfree(c->d_gpre);
-  dfree(c->d_obins);
-  dfree(c->d_order);
+  c->pool.release(c->d_model);
+  c->pool.release(c->d_counter);
+  for (int k = 0; k < 4; ++k) c->pool.release(c->d_stage[k]);
+  c->pool.release(c->d_seq_hits);
+  c->pool.release(c->d_seq_stats);
+  c->pool.release(c->d_gkeys);
+  c->pool.release(c->d_grec);
+  c->pool.release(c->d_gslot);
+  c->pool.release(c->d_dcnt);
+  c->pool.release(c->d_dlist);
+  c->pool.release(c->d_gpop);
+  c->pool.release(c->d_glist);
+  c->pool.release(c->d_gplist);
+  c->pool.release(c->d_grep);
+  c->pool.release(c->d_gpre);
+  c->pool.release(c->d_obins);
+  c->pool.release(c->d_order);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   if (c->stream) (void)hipStreamDestroy(c->stream);
   if (c->aux) (void)hipStreamDestroy(c->aux);
@@ -485,6 +478,16 @@ const char* ps_last_error(const ps_ctx* c) {
 #define PS_SOURCE_HASH "unknown"
 #endif
 const char* ps_build_id(void) { return PS_SOURCE_HASH; }
+
+// For the tests (not in packserve.h): device allocations of the context fail as
+// out of memory where it would hold more than `bytes` (0: no limit); *held (if
+// not NULL): what it holds now.
+ps_status ps_test_limit_memory(ps_ctx* c, int64_t bytes, int64_t* held) {
+  if (!c || bytes < 0) return fail(c, PS_E_INVAL, "ctx is NULL or the limit negative");
+  c->pool.set_limit((size_t)bytes);
+  if (held) *held = (int64_t)c->pool.held();
+  return PS_OK;
+}
 
 ps_status ps_load_instances(ps_ctx* c, const ps_instances* in, const ps_model* m) {
   if (!c) return fail(nullptr, PS_E_INVAL, "ctx is NULL");
@@ -700,30 +703,30 @@ static ps_status group_buffers(ps_ctx* c, int32_t n_req, hipStream_t s) {
   while (want < 2u * (uint32_t)n_req) want <<= 1;
   bool clear = false;
   if (want > c->gslots) {
-    dfree(c->d_gkeys);
-    dfree(c->d_grec);
+    c->pool.release(c->d_gkeys);
+    c->pool.release(c->d_grec);
     c->gslots = 0;
-    HIP_TRY(c, hipMalloc((void**)&c->d_gkeys, 2 * (size_t)want * sizeof(unsigned long long)));
-    HIP_TRY(c, hipMalloc((void**)&c->d_grec, (size_t)want * kGroupRec * sizeof(uint2)));
+    HIP_TRY(c, c->pool.grow(&c->d_gkeys, 2 * (size_t)want * sizeof(unsigned long long)));
+    HIP_TRY(c, c->pool.grow(&c->d_grec, (size_t)want * kGroupRec * sizeof(uint2)));
     c->gslots = want;
     clear = true;
   }
   if (!c->d_gpop) {
     // two halves of rows: the walk pass's, then the popular pass's
-    HIP_TRY(c, hipMalloc((void**)&c->d_gpop, 2 * kGroupPopBytes + kGroupHeadWords * sizeof(uint32_t)));
+    HIP_TRY(c, c->pool.grow(&c->d_gpop, 2 * kGroupPopBytes + kGroupHeadWords * sizeof(uint32_t)));
     HIP_TRY(c, hipMemsetAsync(c->d_gpop, 0, kGroupHeadWords * sizeof(uint32_t), s));  // counter words
   }
   const uint32_t lcap = leader_list_cap(n_req);
   if (lcap > c->glcap) {
-    dfree(c->d_glist);
+    c->pool.release(c->d_glist);
     c->glcap = 0;
-    HIP_TRY(c, hipMalloc((void**)&c->d_glist, (size_t)kXcds * lcap * sizeof(unsigned long long)));
+    HIP_TRY(c, c->pool.grow(&c->d_glist, (size_t)kXcds * lcap * sizeof(unsigned long long)));
     c->glcap = lcap;
   }
   if (n_req > c->greq_cap) {
-    dfree(c->d_gslot);
+    c->pool.release(c->d_gslot);
     c->greq_cap = 0;
-    HIP_TRY(c, hipMalloc((void**)&c->d_gslot, (size_t)n_req * sizeof(uint32_t)));
+    HIP_TRY(c, c->pool.grow(&c->d_gslot, (size_t)n_req * sizeof(uint32_t)));
     c->greq_cap = n_req;
   }
   // the popular pass lists at most one entry per group: no more than the
@@ -733,23 +736,23 @@ static ps_status group_buffers(ps_ctx* c, int32_t n_req, hipStream_t s) {
   bool clear_rep = false;
   if (popular_pass_ok(c)) {
     if (pcap > c->gplist_cap) {
-      dfree(c->d_gplist);
+      c->pool.release(c->d_gplist);
       c->gplist_cap = 0;
-      HIP_TRY(c, hipMalloc((void**)&c->d_gplist, (size_t)pcap * sizeof(uint2)));
+      HIP_TRY(c, c->pool.grow(&c->d_gplist, (size_t)pcap * sizeof(uint2)));
       c->gplist_cap = pcap;
     }
     if (c->x.n_pop > c->grep_cap) {
-      dfree(c->d_grep);
+      c->pool.release(c->d_grep);
       c->grep_cap = 0;
-      HIP_TRY(c, hipMalloc((void**)&c->d_grep, (size_t)c->x.n_pop * sizeof(unsigned long long)));
+      HIP_TRY(c, c->pool.grow(&c->d_grep, (size_t)c->x.n_pop * sizeof(unsigned long long)));
       c->grep_cap = c->x.n_pop;
       clear_rep = true;
     }
     const size_t pre_words = (size_t)c->x.n_pop * ((size_t)c->n_inst + 1);
     if (pre_words > c->gpre_cap) {
-      dfree(c->d_gpre);
+      c->pool.release(c->d_gpre);
       c->gpre_cap = 0;
-      HIP_TRY(c, hipMalloc((void**)&c->d_gpre, pre_words * sizeof(uint32_t)));
+      HIP_TRY(c, c->pool.grow(&c->d_gpre, pre_words * sizeof(uint32_t)));
       c->gpre_cap = pre_words;
     }
   }
@@ -806,11 +809,11 @@ static ps_status launch_score(ps_ctx* c, const uint64_t* d_pool, int64_t pool_le
   const bool probe_all = d_hits != nullptr;
   if (probe_all) {  // longest chains first
     if (!c->d_obins)
-      HIP_TRY(c, hipMalloc((void**)&c->d_obins, kOrderAll * sizeof(uint32_t)));
+      HIP_TRY(c, c->pool.grow(&c->d_obins, kOrderAll * sizeof(uint32_t)));
     if (n_req > c->order_cap) {
-      dfree(c->d_order);
+      c->pool.release(c->d_order);
       c->order_cap = 0;
-      HIP_TRY(c, hipMalloc((void**)&c->d_order, (size_t)n_req * sizeof(int32_t)));
+      HIP_TRY(c, c->pool.grow(&c->d_order, (size_t)n_req * sizeof(int32_t)));
       c->order_cap = n_req;
     }
     HIP_TRY(c, ps_launch_order(d_reqs, n_req, pool_len, c->d_obins, c->d_order, s));
@@ -890,11 +893,11 @@ static ps_status launch_score(ps_ctx* c, const uint64_t* d_pool, int64_t pool_le
       const int64_t batches_w = (n_batch + rows_grid - 1) / rows_grid;
       const int64_t cap = waves_q * batches_w * 4;
       if (!c->d_dcnt)
-        HIP_TRY(c, hipMalloc((void**)&c->d_dcnt, (size_t)kDeferLists * kDeferStride * sizeof(uint32_t)));
+        HIP_TRY(c, c->pool.grow(&c->d_dcnt, (size_t)kDeferLists * kDeferStride * sizeof(uint32_t)));
       if (cap > c->dcap) {
-        dfree(c->d_dlist);
+        c->pool.release(c->d_dlist);
         c->dcap = 0;
-        HIP_TRY(c, hipMalloc((void**)&c->d_dlist, (size_t)kDeferLists * (size_t)cap * sizeof(int32_t)));
+        HIP_TRY(c, c->pool.grow(&c->d_dlist, (size_t)kDeferLists * (size_t)cap * sizeof(int32_t)));
         c->dcap = cap;
       }
       a.dcnt = c->d_dcnt;
@@ -1411,7 +1414,7 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
                                 hipStream_t s) {
   const int32_t ni = c->n_inst;
   HIP_TRY(c, hipMemsetAsync(c->d_counter, 0, sizeof(unsigned long long), s));
-  if (!c->d_seq_stats) HIP_TRY(c, hipMalloc(&c->d_seq_stats, 2 * sizeof(unsigned long long)));
+  if (!c->d_seq_stats) HIP_TRY(c, c->pool.grow(&c->d_seq_stats, 2 * sizeof(unsigned long long)));
   HIP_TRY(c, hipMemsetAsync(c->d_seq_stats, 0, 2 * sizeof(unsigned long long), s));
   // Batches: Algorithm 1 with a keyed selector (the Random and H-C-Q choices
   // are not a least key)
@@ -1426,9 +1429,9 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
   const int32_t chunk = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)(n_req - r_first), c->seq_budget / per_req));
   if (r_first < n_req && (size_t)chunk * (size_t)ni > c->seq_hits_cap) {
     const size_t need = (size_t)chunk * (size_t)ni;
-    dfree(c->d_seq_hits);
+    c->pool.release(c->d_seq_hits);
     c->seq_hits_cap = 0;
-    HIP_TRY(c, hipMalloc(&c->d_seq_hits, need * sizeof(uint32_t)));
+    HIP_TRY(c, c->pool.grow(&c->d_seq_hits, need * sizeof(uint32_t)));
     c->seq_hits_cap = need;
   }
   const int threads = kSeqMaxThreads;  // every step of a request uses the whole workgroup

@@ -7,6 +7,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <vector>
 
 #include "packserve.h"
@@ -429,21 +430,29 @@ struct BuildArgs {
   uint32_t* rank;            // n_blk: exclusive scan of `won` (global)
 };
 
-// Device memory a context uses again: a snapshot load and an index build take
-// a dozen buffers each and give as many back, and hipMalloc / hipFree cost 78
-// and 108 us a call here (18 of the 30 ms of a load and four commits on a pool
-// of 64).  Idle buffers are kept up to kPoolIdleMax bytes (one snapshot of the
-// largest benchmark window), the oldest going back to the device beyond that
-// or when an allocation fails, all of them at drain().  One pool per context,
-// under the context's rules for threads.  put() waits for the device, as
-// hipFree does, so no stream still reads a buffer that is handed out again.
+// Device memory of a context.  get / put: buffers it uses again.  A snapshot
+// load and an index build take a dozen buffers each and give as many back, and
+// hipMalloc / hipFree cost 78 and 108 us a call here (18 of the 30 ms of a load
+// and four commits on a pool of 64).  Idle buffers are kept up to twice the
+// bytes in use (a reload leaves the old snapshot and the build's temporaries
+// behind, less than twice the new one) and to kPoolIdleMax, the oldest going
+// back to the device beyond that.  put() waits for the device, as hipFree does,
+// so no stream still reads a buffer that is handed out again.  grow / release:
+// buffers that stay until they are outgrown, straight from and to the device.
+// An allocation that fails is tried again without the idle buffers of this
+// context, then without those of every context on the device: nobody runs out
+// of memory that only lies idle.  One pool per context, under the context's
+// rules for threads; what other contexts may take (the idle list) is locked.
 class DevPool {
  public:
-  ~DevPool() { drain(); }
-  hipError_t get(void** out, size_t bytes);
+  DevPool();
+  ~DevPool();
+  DevPool(const DevPool&) = delete;
+  DevPool& operator=(const DevPool&) = delete;
+  void set_device(int device) { device_ = device; }
   template <class T>
   hipError_t get(T** out, size_t bytes) {
-    return get((void**)out, bytes);
+    return get_block((void**)out, bytes);
   }
   // Gives back every non-null pointer of the list and clears it.
   template <class... T>
@@ -455,15 +464,37 @@ class DevPool {
     (put_idle((void*)p), ...);
     ((p = nullptr), ...);
   }
+  template <class T>
+  hipError_t grow(T** out, size_t bytes) {
+    return device_alloc((void**)out, bytes);
+  }
+  template <class T>
+  void release(T*& p) {
+    free_block((void*)p);
+    p = nullptr;
+  }
   void drain();
+  // Test hook: device allocations fail as out of memory where the context
+  // would hold more than `bytes` (0: no limit).
+  void set_limit(size_t bytes) { limit_ = bytes; }
+  size_t held();
 
  private:
   struct Block {
     void* p;
     size_t bytes;
   };
+  bool reserve_live();
+  hipError_t get_block(void** out, size_t bytes);
   void put_idle(void* p);
-  std::vector<Block> live_, idle_;
+  hipError_t device_alloc(void** out, size_t bytes);
+  void free_block(void* p);
+  int device_ = 0;
+  size_t limit_ = 0;
+  std::vector<Block> live_;
+  size_t live_bytes_ = 0;
+  std::mutex mu_;  // the idle list
+  std::vector<Block> idle_;
   size_t idle_bytes_ = 0;
 };
 constexpr size_t kPoolIdleMax = (size_t)4 << 30;

@@ -316,61 +316,6 @@ __global__ __launch_bounds__(64) void bitmap_kernel(GIndex x, const uint32_t* rs
 
 }  // namespace
 
-hipError_t DevPool::get(void** out, size_t bytes) {
-  *out = nullptr;
-  if (bytes == 0) bytes = 1;
-  // the smallest idle buffer that fits and is at most twice as large (or
-  // small anyway)
-  size_t best = idle_.size();
-  for (size_t k = 0; k < idle_.size(); ++k)
-    if (idle_[k].bytes >= bytes && idle_[k].bytes <= 2 * bytes + 65536 &&
-        (best == idle_.size() || idle_[k].bytes < idle_[best].bytes))
-      best = k;
-  if (best < idle_.size()) {
-    const Block b = idle_[best];
-    idle_.erase(idle_.begin() + (long)best);
-    idle_bytes_ -= b.bytes;
-    live_.push_back(b);
-    *out = b.p;
-    return hipSuccess;
-  }
-  hipError_t e = hipMalloc(out, bytes);
-  if (e == hipErrorOutOfMemory && !idle_.empty()) {
-    (void)hipGetLastError();
-    drain();
-    e = hipMalloc(out, bytes);
-  }
-  if (e != hipSuccess) {
-    *out = nullptr;
-    return e;
-  }
-  live_.push_back(Block{*out, bytes});
-  return hipSuccess;
-}
-
-void DevPool::put_idle(void* p) {
-  if (!p) return;
-  for (size_t k = 0; k < live_.size(); ++k) {
-    if (live_[k].p != p) continue;
-    const Block b = live_[k];
-    live_.erase(live_.begin() + (long)k);
-    idle_.push_back(b);
-    idle_bytes_ += b.bytes;
-    break;
-  }
-  while (idle_bytes_ > kPoolIdleMax) {
-    (void)hipFree(idle_.front().p);
-    idle_bytes_ -= idle_.front().bytes;
-    idle_.erase(idle_.begin());
-  }
-}
-
-void DevPool::drain() {
-  for (const Block& b : idle_) (void)hipFree(b.p);
-  idle_.clear();
-  idle_bytes_ = 0;
-}
-
 void ps_free_index(GIndex* x, DevPool* pool) {
   pool->put(x->ent, x->holders, x->bitmaps);
   x->bmask = 0;

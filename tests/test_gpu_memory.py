@@ -1,0 +1,91 @@
+"""Device memory of a context: an allocation that fails takes back what lies
+idle, in this context and in others."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from tests.gpu_util import DeviceWindow, compare_decisions, load_window
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def ps():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_33224_amd as ps
+    return ps
+
+
+@pytest.fixture()
+def scorer(ps):
+    s = ps.Scorer(0)
+    yield s
+    s.close()
+
+
+def limit(scorer, n_bytes):
+    """Device memory the context may hold from now on (0: no limit); returns
+    what it holds."""
+    import paper_2609_33224_amd as ps
+    f = ps.load_library().ps_test_limit_memory
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
+    f.restype = ctypes.c_int32
+    held = ctypes.c_int64()
+    assert f(scorer.ctx, int(n_bytes), ctypes.byref(held)) == 0
+    return held.value
+
+
+def _window(seed, cap=20000):
+    return synth.generate("c2", seed=seed, n_req=256, n_sess=64, cap=cap)
+
+
+def test_growth_takes_back_idle_memory(scorer):
+    """A second load leaves the first snapshot's buffers idle; the first
+    scoring call then needs its group table (128 MiB and more), which fits
+    only where the idle buffers were."""
+    w = _window(1, cap=200000)
+    load_window(scorer, w)
+    load_window(scorer, w)
+    held = limit(scorer, 0)
+    limit(scorer, held + 16 * MIB)
+    res, sizes = DeviceWindow(w).score(scorer)
+    compare_decisions(res, sizes, oracle.Oracle.from_window(w).window_score(w))
+    limit(scorer, 0)
+
+
+def test_idle_memory_follows_the_snapshot(scorer):
+    """After a small snapshot the context keeps no more than three times what
+    it uses, whatever was loaded before."""
+    small = _window(2, cap=4096)
+    load_window(scorer, small)
+    load_window(scorer, small)
+    a = limit(scorer, 0)
+    load_window(scorer, _window(3, cap=200000))
+    load_window(scorer, small)
+    b = limit(scorer, 0)
+    assert b <= 3 * a, (a, b)
+
+
+def test_idle_memory_of_another_context(ps, scorer):
+    """What another context keeps idle is given back where this one runs out
+    (a limit no release can meet: every context is asked)."""
+    other = ps.Scorer(0)
+    w = _window(6, cap=200000)
+    load_window(other, w)
+    load_window(other, w)
+    before = limit(other, 0)
+    load_window(scorer, _window(7))
+    limit(scorer, 1)
+    with pytest.raises(ps.PackServeError):
+        DeviceWindow(w).score(scorer)
+    assert limit(other, 0) < before
+    res, sizes = DeviceWindow(w).score(other)
+    compare_decisions(res, sizes, oracle.Oracle.from_window(w).window_score(w))
+    other.close()
