@@ -169,6 +169,7 @@ struct ps_ctx {
   int32_t* d_dlist = nullptr;
   int64_t dcap = 0;
   uint64_t ggen = 0;
+  bool gclear = false, grep_clear = false;  // to be cleared before the next window's launches
   uint2* d_gplist = nullptr;  // the popular pass's groups
   uint32_t gplist_cap = 0;
   unsigned long long* d_grep = nullptr;  // representatives, per holder bitmap
@@ -696,12 +697,12 @@ static bool popular_pass_ok(const ps_ctx* c) {
 }
 
 // Group table for a window of n_req requests (at least two slots per
-// request) and the next window generation.  Grows (and clears) only when a
-// larger window arrives; a wrapped generation clears the keys once.
-static ps_status group_buffers(ps_ctx* c, int32_t n_req, hipStream_t s) {
+// request).  Grows only when a larger window arrives; what is new is cleared
+// by group_window, also where a later allocation of this call fails: an
+// uncleared tagged length would send a walk past the pool's end.
+static ps_status group_buffers(ps_ctx* c, int32_t n_req) {
   uint32_t want = 64;
   while (want < 2u * (uint32_t)n_req) want <<= 1;
-  bool clear = false;
   if (want > c->gslots) {
     c->pool.release(c->d_gkeys);
     c->pool.release(c->d_grec);
@@ -709,12 +710,12 @@ static ps_status group_buffers(ps_ctx* c, int32_t n_req, hipStream_t s) {
     HIP_TRY(c, c->pool.grow(&c->d_gkeys, 2 * (size_t)want * sizeof(unsigned long long)));
     HIP_TRY(c, c->pool.grow(&c->d_grec, (size_t)want * kGroupRec * sizeof(uint2)));
     c->gslots = want;
-    clear = true;
+    c->gclear = true;
   }
   if (!c->d_gpop) {
     // two halves of rows: the walk pass's, then the popular pass's
     HIP_TRY(c, c->pool.grow(&c->d_gpop, 2 * kGroupPopBytes + kGroupHeadWords * sizeof(uint32_t)));
-    HIP_TRY(c, hipMemsetAsync(c->d_gpop, 0, kGroupHeadWords * sizeof(uint32_t), s));  // counter words
+    c->gclear = true;
   }
   const uint32_t lcap = leader_list_cap(n_req);
   if (lcap > c->glcap) {
@@ -733,7 +734,6 @@ static ps_status group_buffers(ps_ctx* c, int32_t n_req, hipStream_t s) {
   // window's requests, nor than the popular area's rows
   const uint32_t pcap = (uint32_t)std::min<size_t>((size_t)n_req,
                                                    kGroupPopBytes / ((size_t)c->n_inst * sizeof(uint32_t)));
-  bool clear_rep = false;
   if (popular_pass_ok(c)) {
     if (pcap > c->gplist_cap) {
       c->pool.release(c->d_gplist);
@@ -746,7 +746,7 @@ static ps_status group_buffers(ps_ctx* c, int32_t n_req, hipStream_t s) {
       c->grep_cap = 0;
       HIP_TRY(c, c->pool.grow(&c->d_grep, (size_t)c->x.n_pop * sizeof(unsigned long long)));
       c->grep_cap = c->x.n_pop;
-      clear_rep = true;
+      c->grep_clear = true;
     }
     const size_t pre_words = (size_t)c->x.n_pop * ((size_t)c->n_inst + 1);
     if (pre_words > c->gpre_cap) {
@@ -756,16 +756,25 @@ static ps_status group_buffers(ps_ctx* c, int32_t n_req, hipStream_t s) {
       c->gpre_cap = pre_words;
     }
   }
+  return PS_OK;
+}
+
+// The next window generation.  Called when nothing but the launches is left:
+// each window's claim pass clears the list lengths of the next, so a generation
+// without a claim pass would leave the lengths of the window before it.  A
+// wrapped generation clears the keys once.
+static ps_status group_window(ps_ctx* c, hipStream_t s) {
   if (++c->ggen > kGroupGenMax) {
     c->ggen = 1;
-    clear = true;
+    c->gclear = true;
   }
-  if (clear) {
+  if (c->gclear) {
     HIP_TRY(c, hipMemsetAsync(c->d_gkeys, 0, 2 * (size_t)c->gslots * sizeof(unsigned long long), s));
     HIP_TRY(c, hipMemsetAsync(c->d_gpop, 0, kGroupHeadWords * sizeof(uint32_t), s));  // list lengths
   }
-  if ((clear || clear_rep) && c->grep_cap)  // representatives: all ones is above every tag
+  if ((c->gclear || c->grep_clear) && c->grep_cap)  // representatives: all ones is above every tag
     HIP_TRY(c, hipMemsetAsync(c->d_grep, 0xFF, (size_t)c->grep_cap * sizeof(unsigned long long), s));
+  c->gclear = c->grep_clear = false;
   return PS_OK;
 }
 
@@ -819,35 +828,12 @@ static ps_status launch_score(ps_ctx* c, const uint64_t* d_pool, int64_t pool_le
     HIP_TRY(c, ps_launch_order(d_reqs, n_req, pool_len, c->d_obins, c->d_order, s));
     a.req_order = c->d_order;
   }
-  if (!probe_all && fixed) {
-    a.grp = *fixed;
-    a.defer_any = fixed->pop_ctr + 1;
-  } else if (!probe_all && n_req <= kGroupMaxReq && pool_len < ((int64_t)1 << kGroupGenShift) - 1) {
-    ps_status st = group_buffers(c, n_req, s);
+  const bool own_groups =
+      !probe_all && !fixed && n_req <= kGroupMaxReq && pool_len < ((int64_t)1 << kGroupGenShift) - 1;
+  const bool groups = own_groups || (!probe_all && fixed);
+  if (own_groups) {
+    const ps_status st = group_buffers(c, n_req);
     if (st != PS_OK) return st;
-    a.grp = GroupTab{c->d_gkeys,
-                     c->d_gkeys + c->gslots,
-                     c->d_grec,
-                     c->d_gslot,
-                     c->d_gpop + kGroupHeadWords,
-                     c->d_gpop,
-                     (uint32_t)(kGroupPopBytes / ((size_t)c->n_inst * sizeof(uint32_t))),
-                     c->gslots - 1u,
-                     c->ggen,
-                     c->d_glist,
-                     c->d_gpop + kListCtrWords * (1u + kXcds * (uint32_t)(c->ggen & 1u)),
-                     c->d_gpop + kListCtrWords * (1u + kXcds * (uint32_t)((c->ggen + 1u) & 1u)),
-                     c->glcap,
-                     // walkers: half the resident waves (8 per CU)
-                     (uint32_t)(8 * c->num_cus),
-                     popular_pass_ok(c) && c->gplist_cap ? 1u : 0u,
-                     c->d_gplist,
-                     c->gplist_cap,
-                     c->d_grep,
-                     c->x.n_pop,
-                     c->d_gpre,
-                     c->d_gpre + (size_t)c->x.n_pop * (size_t)c->n_inst};
-    a.defer_any = c->d_gpop + 1;
   }
   // The scoring kernel takes batches of a.batch requests per wave; a small
   // pool's waves copy the pool's state into LDS once and take batches in
@@ -876,7 +862,7 @@ static ps_status launch_score(ps_ctx* c, const uint64_t* d_pool, int64_t pool_le
   // The lean scorer first when the groups give the requests their hits and
   // the selector is neither Random nor H-C-Q (persistent grid at its own
   // occupancy); the general scorer then finishes what it left.
-  const bool lean = !probe_all && a.grp.keys && a.sel != PS_SEL_RANDOM && a.sel != PS_SEL_HCQ;
+  const bool lean = groups && a.sel != PS_SEL_RANDOM && a.sel != PS_SEL_HCQ;
   const DevModel& hm = c->h_model;
   const bool rows = lean && !d_sizes && hm.mono && !(hm.flags & PS_F_TTFT_ADMIT) &&
                     (a.sel == PS_SEL_DCQ || a.sel == PS_SEL_DQ || a.sel == PS_SEL_DQC) &&
@@ -905,6 +891,36 @@ static ps_status launch_score(ps_ctx* c, const uint64_t* d_pool, int64_t pool_le
       a.dcap = (int32_t)c->dcap;
     }
   }
+  if (groups && fixed) {
+    a.grp = *fixed;
+    a.defer_any = fixed->pop_ctr + 1;
+  } else if (groups) {
+    const ps_status st = group_window(c, s);
+    if (st != PS_OK) return st;
+    a.grp = GroupTab{c->d_gkeys,
+                     c->d_gkeys + c->gslots,
+                     c->d_grec,
+                     c->d_gslot,
+                     c->d_gpop + kGroupHeadWords,
+                     c->d_gpop,
+                     (uint32_t)(kGroupPopBytes / ((size_t)c->n_inst * sizeof(uint32_t))),
+                     c->gslots - 1u,
+                     c->ggen,
+                     c->d_glist,
+                     c->d_gpop + kListCtrWords * (1u + kXcds * (uint32_t)(c->ggen & 1u)),
+                     c->d_gpop + kListCtrWords * (1u + kXcds * (uint32_t)((c->ggen + 1u) & 1u)),
+                     c->glcap,
+                     // walkers: half the resident waves (8 per CU)
+                     (uint32_t)(8 * c->num_cus),
+                     popular_pass_ok(c) && c->gplist_cap ? 1u : 0u,
+                     c->d_gplist,
+                     c->gplist_cap,
+                     c->d_grep,
+                     c->x.n_pop,
+                     c->d_gpre,
+                     c->d_gpre + (size_t)c->x.n_pop * (size_t)c->n_inst};
+    a.defer_any = c->d_gpop + 1;
+  }
   if (ev) HIP_TRY(c, hipEventRecord(ev[0], s));
   // the walk pass over the leaders' lists: a wave per four requests (about
   // two waves per group at the usual group sizes), so the dispatcher
@@ -914,7 +930,9 @@ static ps_status launch_score(ps_ctx* c, const uint64_t* d_pool, int64_t pool_le
   if (a.grp.keys) {
     const int split = std::min((int)kGroupSplitMax * n_req, 8 * c->num_cus);
     const int walk_grid = std::max(64, (std::max(n_req / 4, split) + 63) / 64 * 64);
+    c->gclear |= own_groups;  // (a claim pass that was not launched leaves its lists uncleared)
     HIP_TRY(c, ps_launch_group(a, walk_grid, s, ev ? ev[1] : nullptr, c->aux, c->fork_ev, c->join_ev));
+    if (own_groups) c->gclear = false;
   } else if (ev) {
     HIP_TRY(c, hipEventRecord(ev[1], s));
   }

@@ -1,5 +1,6 @@
 """Device memory of a context: an allocation that fails takes back what lies
-idle, in this context and in others."""
+idle, in this context and in others, and a call that cannot get its memory
+leaves the context as it was."""
 import ctypes
 
 import numpy as np
@@ -71,6 +72,59 @@ def test_idle_memory_follows_the_snapshot(scorer):
     load_window(scorer, small)
     b = limit(scorer, 0)
     assert b <= 3 * a, (a, b)
+
+
+def test_out_of_memory_is_an_error_and_no_more(ps, scorer):
+    """Loads and scoring calls that cannot get their memory: PS_E_NOMEM, the
+    snapshot as before, and the next call works."""
+    w, other = _window(4), _window(5, cap=400000)
+    load_window(scorer, w)
+    want = scorer.state()
+    limit(scorer, 1)
+    dw = DeviceWindow(w)
+    for call in (lambda: load_window(scorer, other), lambda: dw.score(scorer)):
+        with pytest.raises(ps.PackServeError) as e:
+            call()
+        assert e.value.code == ps.binding.PS_E_NOMEM
+    limit(scorer, 0)
+    for k, v in scorer.state().items():
+        assert (v == want[k]).all(), k
+    res, sizes = dw.score(scorer)
+    compare_decisions(res, sizes, oracle.Oracle.from_window(w).window_score(w))
+
+
+@pytest.mark.parametrize("popular", [False, True])
+def test_scoring_that_ran_out_scores_again(ps, scorer, popular):
+    """A larger window whose tables grow only in part, for a range of limits,
+    after windows of both parities: PS_E_NOMEM, then the same decisions as
+    without a limit (the half-grown group table is cleared first, and no
+    window's leader lists are those of an earlier one)."""
+    kw = dict(sp_frac=0.9, sp_blocks=64, n_inst=96) if popular else {}
+    large = synth.generate("c2", seed=8, n_req=6000, n_sess=64, cap=20000, **kw)
+    small = large.subset(range(64))
+    d_small, d_large = DeviceWindow(small), DeviceWindow(large)
+    want = oracle.Oracle.from_window(large).window_score(large)
+    failed = 0
+    for k in range(24):
+        s = ps.Scorer(0)
+        load_window(s, large)
+        limit(s, 1)  # gives the load's idle buffers back
+        with pytest.raises(ps.PackServeError):
+            d_small.score(s, with_sizes=False)
+        limit(s, 0)
+        for _ in range(2 + k % 2):
+            d_small.score(s, with_sizes=False)
+        limit(s, limit(s, 0) + int(1000 * 1.45 ** k))
+        try:
+            d_large.score(s, with_sizes=False)
+        except ps.PackServeError as e:
+            assert e.code == ps.binding.PS_E_NOMEM
+            failed += 1
+        limit(s, 0)
+        for sizes in (False, True):
+            compare_decisions(*d_large.score(s, with_sizes=sizes), want, label=f"limit {k}")
+        s.close()
+    assert 0 < failed < 24, failed
 
 
 def test_idle_memory_of_another_context(ps, scorer):
