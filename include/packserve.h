@@ -17,7 +17,10 @@
  * Conventions shared by every entry point:
  *   - Return value: PS_OK (0) or a negative PS_E_* code.  Nothing is thrown
  *     or aborted across the ABI; ps_last_error() gives the message.  On an
- *     error the outputs are unspecified and the context state is unchanged.
+ *     error the outputs are unspecified and the context state is unchanged;
+ *     a call that fails after it began to change the snapshot (a failing
+ *     device, or no memory to rebuild the prefix index after placements)
+ *     leaves the context without one: PS_E_STATE until the next load.
  *   - Host pointers are owned by the caller; the library copies what it
  *     needs before returning and keeps no pointer to them.
  *   - "_dev" entry points take device pointers owned by the caller, enqueue
@@ -361,7 +364,9 @@ ps_status ps_replay_window_dev(ps_ctx* ctx, const uint64_t* d_pool, int64_t pool
  * (L - block_tokens * hit), S_i += L, and the chain's blocks enter
  * the table in chain order until table_cap_blocks distinct blocks are held;
  * refused blocks are counted in *n_dropped.  No eviction.  Synchronous.
- * PS_E_RANGE if a counter would leave its limit.
+ * Takes 28 bytes of device workspace per chain position, at most 2^24
+ * positions (448 MiB) at a time, fewer where the device has no room for that
+ * (one chain at least).  PS_E_RANGE if a counter would leave its limit.
  */
 ps_status ps_commit(ps_ctx* ctx, const uint64_t* pool, int64_t pool_len, const ps_req* reqs,
                     const int32_t* inst, int32_t n, int64_t* n_dropped);

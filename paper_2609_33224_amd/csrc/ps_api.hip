@@ -141,14 +141,16 @@ struct ps_ctx {
   int64_t lout_seen = 0;
   float lout_raw = 0.0f;
   // staging for the host-memory entry points
-  void* d_stage[4] = {nullptr, nullptr, nullptr, nullptr};  // [3]: commit workspace
-  size_t stage_cap[4] = {0, 0, 0, 0};
+  void* d_stage[3] = {nullptr, nullptr, nullptr};
+  size_t stage_cap[3] = {0, 0, 0};
   // per-arrival scheduler: hits of one launch's requests on every instance
   uint32_t* d_seq_hits = nullptr;
   size_t seq_hits_cap = 0;  // elements
   size_t seq_budget = (size_t)256 << 20;  // bytes of hits per scheduler launch
   // speculative batches (requests per batch; 0: every request scored in full)
   int32_t spec_batch = kSpecBatch;
+  // chain positions of a commit's slice and of a scheduling batch at most
+  int64_t max_pos = kCommitMaxPos;
   unsigned long long* d_seq_stats = nullptr;     // decisions from speculation, scored in full
   // prefix groups of the scored windows: slot keys (tagged with a window
   // generation, so a new window needs no clearing), slot records, and each
@@ -447,7 +449,7 @@ ps_status ps_destroy(ps_ctx* c) {
   free_snapshot(c);
   c->pool.release(c->d_model);
   c->pool.release(c->d_counter);
-  for (int k = 0; k < 4; ++k) c->pool.release(c->d_stage[k]);
+  for (int k = 0; k < 3; ++k) c->pool.release(c->d_stage[k]);
   c->pool.release(c->d_seq_hits);
   c->pool.release(c->d_seq_stats);
   c->pool.release(c->d_gkeys);
@@ -487,6 +489,14 @@ ps_status ps_test_limit_memory(ps_ctx* c, int64_t bytes, int64_t* held) {
   if (!c || bytes < 0) return fail(c, PS_E_INVAL, "ctx is NULL or the limit negative");
   c->pool.set_limit((size_t)bytes);
   if (held) *held = (int64_t)c->pool.held();
+  return PS_OK;
+}
+
+// For the tests: positions of a commit's slice and of a scheduling batch at
+// most (0: the default).
+ps_status ps_test_limit_positions(ps_ctx* c, int64_t n) {
+  if (!c || n < 0 || n > (int64_t)kCommitMaxPos) return fail(c, PS_E_INVAL, "ctx is NULL or the limit out of range");
+  c->max_pos = n ? n : (int64_t)kCommitMaxPos;
   return PS_OK;
 }
 
@@ -1127,11 +1137,27 @@ ps_status ps_score_window(ps_ctx* c, const uint64_t* pool, int64_t pool_len, con
   return zero == ~0ull ? PS_OK : zero_hash(c, "pool", zero);
 }
 
+// A call that began to change the snapshot and could not end: what is left is
+// neither the old state nor the new one, so the context has none.
+static ps_status lose_snapshot(ps_ctx* c, ps_status st) {
+  free_snapshot(c);
+  c->err += "; the snapshot is lost, load it again";
+  return st;
+}
+
+// Gives a pool buffer back at the end of the scope.
+struct PoolScope {
+  DevPool& pool;
+  unsigned char*& p;
+  ~PoolScope() { pool.put(p); }
+};
+
 // After placements were committed on the device (work queued on `s`, the
 // dropped-block count in d_counter): read the counters back and rebuild the
 // derived data the window kernel reads (sorted rooms, key order, prefix
-// index).  Synchronous.
-static ps_status after_commit(ps_ctx* c, hipStream_t s, int64_t* n_dropped) {
+// index).  ws: the placements' workspace, given back before the index needs
+// memory.  Synchronous.
+static ps_status refresh_committed(ps_ctx* c, hipStream_t s, unsigned char*& ws, int64_t* n_dropped) {
   unsigned long long dropped = 0;
   HIP_TRY(c, ps_launch_derive(derive_args(*c, c->n_inst, c->h_model), s));
   HIP_TRY(c, hipMemcpyAsync(&dropped, c->d_counter, sizeof dropped, hipMemcpyDeviceToHost, s));
@@ -1140,6 +1166,7 @@ static ps_status after_commit(ps_ctx* c, hipStream_t s, int64_t* n_dropped) {
   HIP_TRY(c, hipMemcpyAsync(c->h_count.data(), c->t.count, c->h_count.size() * sizeof(uint32_t),
                             hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
+  c->pool.put(ws);
   HIP_TRY(c, ps_build_index(c->t, c->n_inst, c->h_count.data(), &c->x, &c->pool, s));
   HIP_TRY(c, hipStreamSynchronize(s));
   const ps_status lst = refresh_lmax(c);
@@ -1148,14 +1175,21 @@ static ps_status after_commit(ps_ctx* c, hipStream_t s, int64_t* n_dropped) {
   return PS_OK;
 }
 
-// Places entries [k0, k1) of a commit on the device, grouped by instance
-// with array order kept inside a group (host arrays reqs and inst; d_reqs
-// the same requests on the device).  keep: uploads that must outlive the
-// stream's copies.
-static ps_status commit_slice(ps_ctx* c, const uint64_t* d_pool, const ps_req* d_reqs,
-                              const ps_req* reqs, const int32_t* inst, int32_t k0, int32_t k1,
-                              std::vector<std::vector<uint32_t>>* keep, hipStream_t s) {
-  const int32_t ni = c->n_inst;
+static ps_status after_commit(ps_ctx* c, hipStream_t s, unsigned char*& ws, int64_t* n_dropped) {
+  const ps_status st = refresh_committed(c, s, ws, n_dropped);
+  return st == PS_OK ? st : lose_snapshot(c, st);
+}
+
+// Entries [k0, k1) of a commit grouped by instance, array order kept inside a
+// group: {header, ent_req, ent_grp, grp_inst, grp_ent, ent_off} in words `at`
+// .. of the call's upload.
+struct CommitSlice {
+  size_t at;
+  uint32_t n_ent, n_grp, n_pos;
+};
+
+static CommitSlice plan_slice(const ps_req* reqs, const int32_t* inst, int32_t k0, int32_t k1, int32_t ni,
+                              std::vector<uint32_t>* upload) {
   std::vector<uint32_t> start((size_t)ni + 1, 0);
   for (int32_t k = k0; k < k1; ++k)
     if (inst[k] >= 0) ++start[(size_t)inst[k] + 1];
@@ -1165,11 +1199,10 @@ static ps_status commit_slice(ps_ctx* c, const uint64_t* d_pool, const ps_req* d
     start[(size_t)i + 1] += start[(size_t)i];
   }
   const uint32_t n_ent = start[(size_t)ni];
-  if (n_ent == 0) return PS_OK;
-  // {header, ent_req, ent_grp, grp_inst, grp_ent, ent_off} in one upload
-  keep->emplace_back(4 + 3 * (size_t)n_ent + 1 + 2 * (size_t)n_grp + 1);
-  std::vector<uint32_t>& up = keep->back();
-  uint32_t* ent_req = up.data() + 4;
+  CommitSlice sl{(upload->size() + 3) & ~(size_t)3, n_ent, n_grp, 0u};
+  upload->resize(sl.at + 4 + 3 * (size_t)n_ent + 1 + 2 * (size_t)n_grp + 1);
+  uint32_t* up = upload->data() + sl.at;
+  uint32_t* ent_req = up + 4;
   uint32_t* ent_grp = ent_req + n_ent;
   uint32_t* grp_inst = ent_grp + n_ent;
   uint32_t* grp_ent = grp_inst + n_grp;
@@ -1197,12 +1230,14 @@ static ps_status commit_slice(ps_ctx* c, const uint64_t* d_pool, const ps_req* d
   up[1] = n_grp;
   up[2] = off;
   up[3] = 0;
-  void *dx, *ws;
-  ps_status st = stage_buffer(c, 2, up.size() * sizeof(uint32_t), &dx);
-  if (st == PS_OK) st = stage_buffer(c, 3, ps_commit_ws_bytes(n_ent, n_grp, off), &ws);
-  if (st != PS_OK) return st;
-  HIP_TRY(c, hipMemcpyAsync(dx, up.data(), up.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-  const uint32_t* d = (const uint32_t*)dx;
+  sl.n_pos = off;
+  return sl;
+}
+
+// Queues a slice (its upload at d_up, the call's workspace at ws).
+static hipError_t launch_slice(ps_ctx* c, const CommitSlice& sl, const uint32_t* d_up, void* ws,
+                               const uint64_t* d_pool, const ps_req* d_reqs, hipStream_t s) {
+  const uint32_t* d = d_up + sl.at;
   CommitBatch b{};
   b.t = c->t;
   b.inst = c->d_inst;
@@ -1210,18 +1245,17 @@ static ps_status commit_slice(ps_ctx* c, const uint64_t* d_pool, const ps_req* d
   b.model = c->d_model;
   b.pool = d_pool;
   b.reqs = d_reqs;
-  b.hdr = (const CommitHdr*)dx;
+  b.hdr = (const CommitHdr*)d;
   b.ent_req = (const int32_t*)(d + 4);
-  b.ent_grp = d + 4 + n_ent;
-  b.grp_inst = (const int32_t*)(d + 4 + 2 * (size_t)n_ent);
-  b.grp_ent = d + 4 + 2 * (size_t)n_ent + n_grp;
-  b.ent_off = d + 4 + 2 * (size_t)n_ent + 2 * (size_t)n_grp + 1;
+  b.ent_grp = d + 4 + sl.n_ent;
+  b.grp_inst = (const int32_t*)(d + 4 + 2 * (size_t)sl.n_ent);
+  b.grp_ent = d + 4 + 2 * (size_t)sl.n_ent + sl.n_grp;
+  b.ent_off = d + 4 + 2 * (size_t)sl.n_ent + 2 * (size_t)sl.n_grp + 1;
   b.cap = (uint32_t)c->cap;
   b.move_state = 1;
   b.dropped = c->d_counter;
-  ps_commit_ws_bind(&b, ws, n_ent, n_grp, off);
-  HIP_TRY(c, ps_launch_commit(b, n_grp, off, s));
-  return PS_OK;
+  ps_commit_ws_bind(&b, ws, sl.n_ent, sl.n_grp, sl.n_pos);
+  return ps_launch_commit(b, sl.n_grp, sl.n_pos, s);
 }
 
 ps_status ps_commit(ps_ctx* c, const uint64_t* pool, int64_t pool_len, const ps_req* reqs,
@@ -1269,25 +1303,51 @@ ps_status ps_commit(ps_ctx* c, const uint64_t* pool, int64_t pool_len, const ps_
   HIP_TRY(c, hipStreamSynchronize(s));
   if (zero != ~0ull) return zero_hash(c, "pool", zero);
   if (placed == 0) return PS_OK;
-  HIP_TRY(c, hipMemcpyAsync(dr, reqs, (size_t)n * sizeof(ps_req), hipMemcpyHostToDevice, s));
-  HIP_TRY(c, hipMemsetAsync(c->d_counter, 0, sizeof(unsigned long long), s));
-  std::vector<std::vector<uint32_t>> keep;
-  // batches of at most kCommitMaxPos chain positions (one entry at least),
-  // in array order
-  for (int32_t k0 = 0; k0 < n;) {
-    int64_t pos = 0;
-    int32_t k1 = k0;
-    for (; k1 < n; ++k1) {
-      const int64_t len = inst[k1] < 0 ? 0 : (int64_t)reqs[k1].pre_len + reqs[k1].tail_len;
-      if (pos > 0 && pos + len > (int64_t)kCommitMaxPos) break;
-      pos += len;
+  // Slices of at most max_pos chain positions (one entry at least), in array
+  // order; where the device has no room for such a workspace, smaller ones.
+  // Everything that may run out does so before the first of them runs.
+  std::vector<uint32_t> upload;
+  std::vector<CommitSlice> slices;
+  unsigned char* ws = nullptr;
+  PoolScope give{c->pool, ws};
+  for (int64_t max_pos = c->max_pos, longest = 0;;) {
+    upload.clear();
+    slices.clear();
+    size_t ws_bytes = 0;
+    int64_t most = 0;
+    for (int32_t k0 = 0; k0 < n;) {
+      int64_t pos = 0;
+      int32_t k1 = k0;
+      for (; k1 < n; ++k1) {
+        const int64_t len = inst[k1] < 0 ? 0 : (int64_t)reqs[k1].pre_len + reqs[k1].tail_len;
+        if (pos > 0 && pos + len > max_pos) break;
+        pos += len;
+        longest = std::max(longest, len);
+      }
+      const CommitSlice sl = plan_slice(reqs, inst, k0, k1, ni, &upload);
+      if (sl.n_ent) slices.push_back(sl);
+      ws_bytes = std::max(ws_bytes, ps_commit_ws_bytes(sl.n_ent, sl.n_grp, sl.n_pos));
+      most = std::max<int64_t>(most, sl.n_pos);
+      k0 = k1;
     }
-    if ((st = commit_slice(c, (const uint64_t*)dp, (const ps_req*)dr, reqs, inst, k0, k1, &keep, s)) !=
-        PS_OK)
-      return st;
-    k0 = k1;
+    const hipError_t e = c->pool.get(&ws, ws_bytes);
+    if (e == hipSuccess) break;
+    if (e != hipErrorOutOfMemory || most <= longest)
+      return fail(c, e == hipErrorOutOfMemory ? PS_E_NOMEM : PS_E_DEVICE, "commit workspace of %.1f MiB: %s",
+                  ws_bytes / 1048576.0, hipGetErrorString(e));
+    max_pos = std::max(longest, most / 2);
   }
-  return after_commit(c, s, n_dropped);
+  void* d_up;
+  if ((st = stage_buffer(c, 2, upload.size() * sizeof(uint32_t), &d_up)) != PS_OK) return st;
+  HIP_TRY(c, hipMemcpyAsync(dr, reqs, (size_t)n * sizeof(ps_req), hipMemcpyHostToDevice, s));
+  HIP_TRY(c, hipMemcpyAsync(d_up, upload.data(), upload.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+  HIP_TRY(c, hipMemsetAsync(c->d_counter, 0, sizeof(unsigned long long), s));
+  for (const CommitSlice& sl : slices) {
+    const hipError_t e =
+        launch_slice(c, sl, (const uint32_t*)d_up, ws, (const uint64_t*)dp, (const ps_req*)dr, s);
+    if (e != hipSuccess) return lose_snapshot(c, fail(c, PS_E_DEVICE, "commit: %s", hipGetErrorString(e)));
+  }
+  return after_commit(c, s, ws, n_dropped);
 }
 
 static bool req_ok_host(const ps_req& q, int64_t pool_len) {
@@ -1319,7 +1379,7 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
     longest = std::max(longest, len_of(r));
     most = std::max(most, run);
   }
-  const uint32_t max_pos = (uint32_t)std::max(longest, std::min(most, (int64_t)kCommitMaxPos));
+  const uint32_t max_pos = (uint32_t)std::max(longest, std::min(most, c->max_pos));
 
   const size_t hits = (size_t)max_n * sched_row_stride(ni) * sizeof(uint32_t);
   const size_t ws_commit = ps_commit_ws_bytes(kSpecBatch, kSpecBatch, max_pos);
@@ -1328,11 +1388,7 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
   const size_t bytes = 2 * (hits + 256) + kSpecBatch * sizeof(SpecRec) +
                        (size_t)kSpecBatch * kSpecBatch * sizeof(uint32_t) + words * sizeof(uint32_t) + ws_commit;
   HIP_TRY(c, c->pool.get(&ws, bytes));
-  struct Give {
-    ps_ctx* c;
-    unsigned char*& p;
-    ~Give() { c->pool.put(p); }
-  } give{c, ws};
+  PoolScope give{c->pool, ws};
   unsigned char* p = ws;
   auto take = [&](size_t n) {
     unsigned char* r = p;
@@ -1474,7 +1530,8 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
               spec ? c->d_seq_stats : nullptr};
     HIP_TRY(c, ps_launch_seq(q, threads, s));
   }
-  return after_commit(c, s, n_dropped);
+  unsigned char* ws = nullptr;
+  return after_commit(c, s, ws, n_dropped);
 }
 
 ps_status ps_set_schedule_budget(ps_ctx* c, int64_t bytes) {

@@ -421,7 +421,7 @@ __global__ __launch_bounds__(64) void commit_state_kernel(CommitBatch b) {
 
 // The workspace of a batch of at most n_ent entries and n_pos positions.
 size_t ps_commit_ws_bytes(uint32_t n_ent, uint32_t n_grp, uint32_t n_pos) {
-  return (size_t)n_pos * (2 * sizeof(uint64_t) + 3 * sizeof(uint32_t)) +
+  return (size_t)n_pos * kCommitPosBytes +
          ((size_t)n_pos / kCommitChunk + 2) * sizeof(uint32_t) + (size_t)n_ent * sizeof(uint32_t) +
          2 * (size_t)n_grp * sizeof(uint32_t) + 16 * 256;
 }

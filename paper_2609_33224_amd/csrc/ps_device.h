@@ -278,6 +278,7 @@ struct CommitHdr {
 };
 constexpr uint32_t kCommitChunkPositions = 1024;  // positions per workgroup and step
 constexpr uint32_t kCommitMaxPos = 1u << 24;      // positions per batch, one chain at least
+constexpr size_t kCommitPosBytes = 2 * sizeof(uint64_t) + 3 * sizeof(uint32_t);  // workspace per position
 struct CommitBatch {
   Tables t;
   InstState* inst;

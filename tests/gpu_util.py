@@ -1,5 +1,7 @@
 """Helpers shared by the GPU tests: marshal a generated window into the C ABI
 and compare GPU decisions with the oracle's."""
+import ctypes
+
 import numpy as np
 
 import oracle
@@ -55,6 +57,27 @@ def edge_window(sets, chains, pool=None, reqs=None, **kw):
     w.beta = np.asarray(w.beta, np.float32)
     w.gamma = np.asarray(w.gamma, np.float32)
     return w
+
+
+def limit_memory(scorer, n_bytes):
+    """Device memory the context may hold from now on (0: no limit); returns
+    what it holds."""
+    import paper_2609_33224_amd as ps
+    f = ps.load_library().ps_test_limit_memory
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
+    f.restype = ctypes.c_int32
+    held = ctypes.c_int64()
+    assert f(scorer.ctx, int(n_bytes), ctypes.byref(held)) == 0
+    return held.value
+
+
+def limit_positions(scorer, n):
+    """Chain positions of a commit's slice and of a scheduling batch at most
+    (0: the default)."""
+    import paper_2609_33224_amd as ps
+    f = ps.load_library().ps_test_limit_positions
+    f.argtypes, f.restype = [ctypes.c_void_p, ctypes.c_int64], ctypes.c_int32
+    assert f(scorer.ctx, int(n)) == 0
 
 
 class DeviceWindow:

@@ -3,12 +3,14 @@ batch taken position by position can go wrong: chains that end at and around a
 chunk of positions, chunks that hold hundreds of short chains, blocks that
 repeat inside a chain and across the chains of one instance, caps that bind
 inside a chain, at a repeat and before the first block, empty chains, and
-placements that skip entries."""
+placements that skip entries; commits cut into slices, and commits that run
+out of device memory."""
 import numpy as np
 import pytest
 
 import oracle
-from tests.gpu_util import DeviceWindow, compare_decisions, edge_window, load_window, nb_cap, reqs_of
+from tests.gpu_util import (DeviceWindow, compare_decisions, edge_window, limit_memory, limit_positions, load_window,
+                            nb_cap, reqs_of)
 
 pytestmark = pytest.mark.gpu
 
@@ -151,3 +153,84 @@ def test_zero_hash_refused(ps, scorer, at):
         assert (before[k] == after[k]).all(), k
     res = scorer.score(w.pool, reqs_of(w))  # the old snapshot still scores
     compare_decisions(res, None, oracle.Oracle.from_window(w).window_score(w))
+
+
+@pytest.mark.parametrize("max_pos", [1, 100, 1024, 3000])
+@pytest.mark.parametrize("cap", [None, 41, 300])
+def test_commit_slices(ps, scorer, max_pos, cap):
+    """A commit cut into slices (blocks that an earlier slice inserted or
+    refused come again in later ones) does what one slice does."""
+    limit_positions(scorer, max_pos)
+    w, inst = _window(max_pos, 3, 150, 5, 90, cap=cap, repeats=0.5, held=40)
+    _check(scorer, w, inst, f"commit in slices of {max_pos}, cap {cap}")
+
+
+def _runs_out(ps, scorer, w, inst, room):
+    """A commit with `room` bytes more than the context holds: PS_E_NOMEM."""
+    load_window(scorer, w)
+    for n_bytes in (1, None):  # 1: gives the load's idle buffers back
+        limit_memory(scorer, n_bytes or limit_memory(scorer, 0) + room)
+        with pytest.raises(ps.PackServeError) as e:
+            scorer.commit(w.pool, reqs_of(w), inst)
+        assert e.value.code == ps.binding.PS_E_NOMEM
+    limit_memory(scorer, 0)
+
+
+def _long_last(long):
+    """Fifty short chains, then one of `long` blocks, on three instances."""
+    chains = [[10 ** 6 + 100 * r + j for j in range(20)] for r in range(50)] + [list(range(1, long + 1))]
+    return edge_window([[5, 6], [7], []], chains, cap=2 * long), np.arange(51, dtype=np.int32) % 3
+
+
+def test_commit_that_runs_out_changes_nothing(ps, scorer):
+    """Memory for the first slices, not for a later, larger one: PS_E_NOMEM
+    before the first placement, and the same commit works afterwards."""
+    w, inst = _long_last(200_000)  # 5.6 MB of workspace for the last chain, 1.6 MB of hashes
+    limit_positions(scorer, 400)
+    _runs_out(ps, scorer, w, inst, 1_700_000 + 500_000)
+    o = oracle.Oracle.from_window(w)
+    so, sg = o.state(), scorer.state()
+    for k in ("D", "Q", "P", "S", "set_size"):
+        assert (so[k] == sg[k]).all(), k
+    dw = DeviceWindow(w)
+    assert (dw.hits(scorer, w.n_inst) == o.window_hits(w)).all()
+    want = o.commit(w.pool, w.pre_off, w.pre_len, w.tail_off, w.tail_len, inst)
+    assert scorer.commit(w.pool, reqs_of(w), inst) == want
+    assert (dw.hits(scorer, w.n_inst) == o.window_hits(w)).all()
+
+
+def test_commit_in_smaller_slices_where_memory_is_short(ps, scorer):
+    """No room for the workspace of the whole commit (35 MB): slices that fit,
+    the same tables."""
+    w = edge_window([[5, 6], [7], []], None, pool=list(range(1, 25_002)), cap=50_000,
+                    reqs=[(r % 2, 25_000 - r, 0, 0) for r in range(50)])
+    inst = (np.arange(50) % 3).astype(np.int32)
+    load_window(scorer, w)
+    limit_memory(scorer, 1)
+    with pytest.raises(ps.PackServeError):
+        DeviceWindow(w).score(scorer)  # gives the idle buffers back
+    limit_memory(scorer, limit_memory(scorer, 0) + 10_000_000)
+    o = oracle.Oracle.from_window(w)
+    want = o.commit(w.pool, w.pre_off, w.pre_len, w.tail_off, w.tail_len, inst)
+    assert scorer.commit(w.pool, reqs_of(w), inst) == want
+    limit_memory(scorer, 0)
+    so, sg = o.state(), scorer.state()
+    for k in ("D", "Q", "P", "S", "set_size"):
+        assert (so[k] == sg[k]).all(), k
+    assert (DeviceWindow(w).hits(scorer, w.n_inst) == o.window_hits(w)).all()
+
+
+def test_commit_whose_index_has_no_room(ps, scorer):
+    """Placements made, no memory to rebuild the prefix index: the context has
+    no snapshot until the next load."""
+    rng = np.random.default_rng(3)
+    sets = [list(rng.integers(1, 1 << 40, 20_000).astype(np.uint64)) for _ in range(32)]
+    w = edge_window(sets, [[1, 2, 3]], cap=30_000)
+    load_window(scorer, w)
+    scorer.commit(w.pool, reqs_of(w), np.array([-1], np.int32))  # the host pool's buffers
+    _runs_out(ps, scorer, w, np.array([0], np.int32), 100_000)
+    for call in (scorer.state, lambda: scorer.score(w.pool, reqs_of(w))):
+        with pytest.raises(ps.PackServeError) as e:
+            call()
+        assert e.value.code == ps.binding.PS_E_STATE
+    _check(scorer, w, np.array([0], np.int32), "after the next load")

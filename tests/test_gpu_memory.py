@@ -1,14 +1,12 @@
 """Device memory of a context: an allocation that fails takes back what lies
 idle, in this context and in others, and a call that cannot get its memory
 leaves the context as it was."""
-import ctypes
-
 import numpy as np
 import pytest
 
 import oracle
 import synth
-from tests.gpu_util import DeviceWindow, compare_decisions, load_window
+from tests.gpu_util import DeviceWindow, compare_decisions, limit_memory, load_window
 
 pytestmark = pytest.mark.gpu
 
@@ -31,18 +29,6 @@ def scorer(ps):
     s.close()
 
 
-def limit(scorer, n_bytes):
-    """Device memory the context may hold from now on (0: no limit); returns
-    what it holds."""
-    import paper_2609_33224_amd as ps
-    f = ps.load_library().ps_test_limit_memory
-    f.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
-    f.restype = ctypes.c_int32
-    held = ctypes.c_int64()
-    assert f(scorer.ctx, int(n_bytes), ctypes.byref(held)) == 0
-    return held.value
-
-
 def _window(seed, cap=20000):
     return synth.generate("c2", seed=seed, n_req=256, n_sess=64, cap=cap)
 
@@ -54,11 +40,11 @@ def test_growth_takes_back_idle_memory(scorer):
     w = _window(1, cap=200000)
     load_window(scorer, w)
     load_window(scorer, w)
-    held = limit(scorer, 0)
-    limit(scorer, held + 16 * MIB)
+    held = limit_memory(scorer, 0)
+    limit_memory(scorer, held + 16 * MIB)
     res, sizes = DeviceWindow(w).score(scorer)
     compare_decisions(res, sizes, oracle.Oracle.from_window(w).window_score(w))
-    limit(scorer, 0)
+    limit_memory(scorer, 0)
 
 
 def test_idle_memory_follows_the_snapshot(scorer):
@@ -67,10 +53,10 @@ def test_idle_memory_follows_the_snapshot(scorer):
     small = _window(2, cap=4096)
     load_window(scorer, small)
     load_window(scorer, small)
-    a = limit(scorer, 0)
+    a = limit_memory(scorer, 0)
     load_window(scorer, _window(3, cap=200000))
     load_window(scorer, small)
-    b = limit(scorer, 0)
+    b = limit_memory(scorer, 0)
     assert b <= 3 * a, (a, b)
 
 
@@ -80,13 +66,13 @@ def test_out_of_memory_is_an_error_and_no_more(ps, scorer):
     w, other = _window(4), _window(5, cap=400000)
     load_window(scorer, w)
     want = scorer.state()
-    limit(scorer, 1)
+    limit_memory(scorer, 1)
     dw = DeviceWindow(w)
     for call in (lambda: load_window(scorer, other), lambda: dw.score(scorer)):
         with pytest.raises(ps.PackServeError) as e:
             call()
         assert e.value.code == ps.binding.PS_E_NOMEM
-    limit(scorer, 0)
+    limit_memory(scorer, 0)
     for k, v in scorer.state().items():
         assert (v == want[k]).all(), k
     res, sizes = dw.score(scorer)
@@ -108,19 +94,19 @@ def test_scoring_that_ran_out_scores_again(ps, scorer, popular):
     for k in range(24):
         s = ps.Scorer(0)
         load_window(s, large)
-        limit(s, 1)  # gives the load's idle buffers back
+        limit_memory(s, 1)  # gives the load's idle buffers back
         with pytest.raises(ps.PackServeError):
             d_small.score(s, with_sizes=False)
-        limit(s, 0)
+        limit_memory(s, 0)
         for _ in range(2 + k % 2):
             d_small.score(s, with_sizes=False)
-        limit(s, limit(s, 0) + int(1000 * 1.45 ** k))
+        limit_memory(s, limit_memory(s, 0) + int(1000 * 1.45 ** k))
         try:
             d_large.score(s, with_sizes=False)
         except ps.PackServeError as e:
             assert e.code == ps.binding.PS_E_NOMEM
             failed += 1
-        limit(s, 0)
+        limit_memory(s, 0)
         for sizes in (False, True):
             compare_decisions(*d_large.score(s, with_sizes=sizes), want, label=f"limit {k}")
         s.close()
@@ -134,12 +120,12 @@ def test_idle_memory_of_another_context(ps, scorer):
     w = _window(6, cap=200000)
     load_window(other, w)
     load_window(other, w)
-    before = limit(other, 0)
+    before = limit_memory(other, 0)
     load_window(scorer, _window(7))
-    limit(scorer, 1)
+    limit_memory(scorer, 1)
     with pytest.raises(ps.PackServeError):
         DeviceWindow(w).score(scorer)
-    assert limit(other, 0) < before
+    assert limit_memory(other, 0) < before
     res, sizes = DeviceWindow(w).score(other)
     compare_decisions(res, sizes, oracle.Oracle.from_window(w).window_score(w))
     other.close()
