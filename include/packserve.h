@@ -302,12 +302,15 @@ ps_status ps_schedule_window_dev(ps_ctx* ctx, const uint64_t* d_pool, int64_t po
                                  uint32_t* d_sizes, int64_t* n_dropped, void* hip_stream);
 
 /*
- * Device memory the two calls above may hold for the hits of the requests
- * one launch schedules (n_inst x 4 bytes per request; the batches of
- * ps_schedule_window_dev, 256 requests at most, hold a list of the walks of
- * the same size beside them): a window whose hits exceed it is scheduled in
- * several launches, in order, with identical results.  0 restores the default, 256 MiB; any budget admits at least one
- * request per launch.  The memory is kept by the context until ps_destroy.
+ * Device memory that the call above and ps_replay_window_dev may take for the
+ * requests one launch schedules: n_inst x 4 bytes per request for its hits and,
+ * for the batches of ps_schedule_window_dev (256 requests at most), as much
+ * again for a list of walks and 28 bytes per chain position (beside them 0.6
+ * MB whatever the budget).  A window that needs more is scheduled in several
+ * launches, in order, with identical results, and without batches where they
+ * do not fit or the device has no memory for them.  0 restores the default,
+ * 256 MiB; any budget admits at least one request per launch.  The hits are
+ * kept until ps_destroy; the rest goes back to the context's idle buffers.
  */
 ps_status ps_set_schedule_budget(ps_ctx* ctx, int64_t bytes);
 

@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -145,7 +146,7 @@ struct ps_ctx {
   size_t stage_cap[3] = {0, 0, 0};
   // per-arrival scheduler: hits of one launch's requests on every instance
   uint32_t* d_seq_hits = nullptr;
-  size_t seq_hits_cap = 0;  // elements
+  size_t seq_hits_cap = 0;  // bytes
   size_t seq_budget = (size_t)256 << 20;  // bytes of hits per scheduler launch
   // speculative batches (requests per batch; 0: every request scored in full)
   int32_t spec_batch = kSpecBatch;
@@ -1356,39 +1357,57 @@ static bool req_ok_host(const ps_req& q, int64_t pool_len) {
          q.tail_len <= pool_len - q.tail_off && (int64_t)q.pre_len + q.tail_len <= PS_MAX_CHAIN;
 }
 
-// Algorithm 1 per arrival in batches (ps_schedule.hip); *taken: requests
-// scheduled (all of them, unless the window's chains share blocks in ways
-// that keep the batches short).  d_counter and the statistics start at zero.
+// Algorithm 1 per arrival in batches (ps_schedule.hip) of at most `rows`
+// requests, whose hits the context holds; *taken: requests scheduled.  All of
+// them, unless the window's chains share blocks in ways that keep the batches
+// short, or the batches' workspace has no room in the budget or on the device
+// (then none).  d_counter and the statistics start at zero.
 static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len, const ps_req* d_reqs,
-                             int32_t n_req, ps_result* d_out, uint32_t* d_sizes, int32_t* taken,
+                             int32_t n_req, uint32_t rows, ps_result* d_out, uint32_t* d_sizes, int32_t* taken,
                              hipStream_t s) {
   const int32_t ni = c->n_inst;
-  const uint32_t max_n = (uint32_t)std::max<size_t>(
-      1, std::min<size_t>((size_t)c->spec_batch, c->seq_budget / ((size_t)ni * sizeof(uint32_t))));
-  // the longest chain and the most positions that max_n requests in a row have
-  std::vector<ps_req> reqs((size_t)n_req);
-  HIP_TRY(c, hipMemcpyAsync(reqs.data(), d_reqs, reqs.size() * sizeof(ps_req), hipMemcpyDeviceToHost, s));
+  *taken = 0;
+  std::unique_ptr<ps_req[]> reqs(new (std::nothrow) ps_req[(size_t)n_req]);
+  if (!reqs) return PS_OK;
+  HIP_TRY(c, hipMemcpyAsync(reqs.get(), d_reqs, (size_t)n_req * sizeof(ps_req), hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
   auto len_of = [&](int32_t r) {
     const ps_req& q = reqs[(size_t)r];
     return req_ok_host(q, pool_len) ? (int64_t)q.pre_len + q.tail_len : 0;
   };
-  int64_t longest = 1, run = 0, most = 1;
+  int64_t longest = 1, total = 0;
+  for (int32_t r = 0; r < n_req; ++r) {
+    total += len_of(r);
+    longest = std::max(longest, len_of(r));
+  }
+  // the budget: per request a row of hits and one of walks, per position the
+  // blocks' set
+  const size_t row = (size_t)sched_row_stride(ni) * sizeof(uint32_t);
+  const size_t mean = (size_t)(total / n_req + 1);
+  const uint32_t max_n =
+      (uint32_t)std::max<size_t>(1, std::min<size_t>(rows, c->seq_budget / (2 * row + mean * kCommitPosBytes)));
+  const size_t hits = (size_t)max_n * row;
+  const int64_t room = c->seq_budget > 2 * hits ? (int64_t)((c->seq_budget - 2 * hits) / kCommitPosBytes) : 0;
+  // the most positions that max_n requests in a row have
+  int64_t run = 0, most = 1;
   for (int32_t r = 0; r < n_req; ++r) {
     run += len_of(r) - (r >= (int32_t)max_n ? len_of(r - (int32_t)max_n) : 0);
-    longest = std::max(longest, len_of(r));
     most = std::max(most, run);
   }
-  const uint32_t max_pos = (uint32_t)std::max(longest, std::min(most, c->max_pos));
+  if (room < longest) return PS_OK;
+  const uint32_t max_pos = (uint32_t)std::max(longest, std::min({most, c->max_pos, room}));
 
-  const size_t hits = (size_t)max_n * sched_row_stride(ni) * sizeof(uint32_t);
   const size_t ws_commit = ps_commit_ws_bytes(kSpecBatch, kSpecBatch, max_pos);
   const size_t words = 32 * (size_t)kSpecBatch;  // the arrays of one word per request
   unsigned char* ws = nullptr;
-  const size_t bytes = 2 * (hits + 256) + kSpecBatch * sizeof(SpecRec) +
-                       (size_t)kSpecBatch * kSpecBatch * sizeof(uint32_t) + words * sizeof(uint32_t) + ws_commit;
-  HIP_TRY(c, c->pool.get(&ws, bytes));
   PoolScope give{c->pool, ws};
+  const size_t bytes = hits + 256 + kSpecBatch * sizeof(SpecRec) +
+                       (size_t)kSpecBatch * kSpecBatch * sizeof(uint32_t) + words * sizeof(uint32_t) + ws_commit;
+  {
+    const hipError_t e = c->pool.get(&ws, bytes);
+    if (e == hipErrorOutOfMemory) return PS_OK;
+    HIP_TRY(c, e);
+  }
   unsigned char* p = ws;
   auto take = [&](size_t n) {
     unsigned char* r = p;
@@ -1411,7 +1430,7 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
   a.out = d_out;
   a.sizes = d_sizes;
   a.stats = c->d_seq_stats;
-  a.hits = (uint32_t*)take(hits);
+  a.hits = c->d_seq_hits;
   a.work = (uint32_t*)take(hits);
   a.spec = (SpecRec*)take(kSpecBatch * sizeof(SpecRec));
   a.lcp = (uint32_t*)take((size_t)kSpecBatch * kSpecBatch * sizeof(uint32_t));
@@ -1463,13 +1482,15 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
   while (done < (uint32_t)n_req) {
     const uint32_t left = (uint32_t)n_req - done;
     const uint32_t rounds = (left + max_n - 1) / max_n;
-    for (uint32_t k = 0; k < rounds; ++k) {
-      HIP_TRY(c, ps_launch_sched_batch(a, s));
-      HIP_TRY(c, ps_launch_commit(b, max_n, max_pos, s));
+    hipError_t e = hipSuccess;
+    for (uint32_t k = 0; k < rounds && e == hipSuccess; ++k) {
+      e = ps_launch_sched_batch(a, s);
+      if (e == hipSuccess) e = ps_launch_commit(b, max_n, max_pos, s);
     }
     uint32_t now = 0;
-    HIP_TRY(c, hipMemcpyAsync(&now, a.cursor, sizeof now, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipStreamSynchronize(s));
+    if (e == hipSuccess) e = hipMemcpyAsync(&now, a.cursor, sizeof now, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return lose_snapshot(c, fail(c, PS_E_DEVICE, "schedule: %s", hipGetErrorString(e)));
     const uint32_t got = now - done;
     done = now;
     if (got < left && (uint64_t)got * 8 < (uint64_t)rounds * std::min(max_n, 128u)) break;
@@ -1494,23 +1515,26 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
   // are not a least key)
   const uint32_t sel = c->h_model.sel;
   const bool spec = !d_forced && c->spec_batch > 0 && sel != PS_SEL_RANDOM && sel != PS_SEL_HCQ;
-  int32_t r_first = 0;
-  if (spec) {
-    const ps_status st = run_batches(c, d_pool, pool_len, d_reqs, n_req, d_out, d_sizes, &r_first, s);
-    if (st != PS_OK) return st;
-  }
-  const size_t per_req = (size_t)ni * sizeof(uint32_t);
-  const int32_t chunk = (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)(n_req - r_first), c->seq_budget / per_req));
-  if (r_first < n_req && (size_t)chunk * (size_t)ni > c->seq_hits_cap) {
-    const size_t need = (size_t)chunk * (size_t)ni;
+  // The hits of a launch's requests, before the first of them is placed (what
+  // the batches leave is scheduled in order in the same rows).
+  const size_t row = (size_t)sched_row_stride(ni) * sizeof(uint32_t);
+  const size_t most = spec ? std::min<size_t>((size_t)n_req, (size_t)c->spec_batch) : (size_t)n_req;
+  const int32_t rows = (int32_t)std::max<size_t>(1, std::min<size_t>(most, c->seq_budget / row));
+  if ((size_t)rows * row > c->seq_hits_cap) {
     c->pool.release(c->d_seq_hits);
     c->seq_hits_cap = 0;
-    HIP_TRY(c, c->pool.grow(&c->d_seq_hits, need * sizeof(uint32_t)));
-    c->seq_hits_cap = need;
+    HIP_TRY(c, c->pool.grow(&c->d_seq_hits, (size_t)rows * row));
+    c->seq_hits_cap = (size_t)rows * row;
+  }
+  int32_t r_first = 0;
+  if (spec) {
+    const ps_status st =
+        run_batches(c, d_pool, pool_len, d_reqs, n_req, (uint32_t)rows, d_out, d_sizes, &r_first, s);
+    if (st != PS_OK) return st;
   }
   const int threads = kSeqMaxThreads;  // every step of a request uses the whole workgroup
-  for (int32_t r0 = r_first; r0 < n_req; r0 += chunk) {
-    const int32_t r1 = std::min(n_req, r0 + chunk);
+  for (int32_t r0 = r_first; r0 < n_req; r0 += rows) {
+    const int32_t r1 = std::min(n_req, r0 + rows);
     ScoreArgs pa{};
     pa.t = c->t;
     pa.x = c->x;
@@ -1524,11 +1548,12 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
     pa.n_inst = ni;
     pa.hits_out = c->d_seq_hits;
     const int grid = std::min(r1 - r0, std::max(1, c->num_cus) * 32);
-    HIP_TRY(c, ps_launch_score(pa, c->hits_in_lds, grid, true, s));
+    hipError_t e = ps_launch_score(pa, c->hits_in_lds, grid, true, s);
     SeqArgs q{c->t, c->d_inst, c->d_room, c->d_model, d_pool, pool_len, d_reqs, r0, r1, ni,
               c->d_seq_hits, d_forced, d_out, d_sizes, (uint32_t)c->cap, c->d_counter,
               spec ? c->d_seq_stats : nullptr};
-    HIP_TRY(c, ps_launch_seq(q, threads, s));
+    if (e == hipSuccess) e = ps_launch_seq(q, threads, s);
+    if (e != hipSuccess) return lose_snapshot(c, fail(c, PS_E_DEVICE, "schedule: %s", hipGetErrorString(e)));
   }
   unsigned char* ws = nullptr;
   return after_commit(c, s, ws, n_dropped);

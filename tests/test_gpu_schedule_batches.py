@@ -3,13 +3,15 @@ again: chains that hold one block at different positions or behind different
 blocks, repeats inside a chain, zero hashes, caps that bind inside a batch and
 instances that are full from the start, tables with holes behind a common
 prefix, malformed descriptors among the requests, and pools on both sides of
-what the deciding workgroup stages in LDS.  Against the in-order scheduler
+what the deciding workgroup stages in LDS, batches cut by their positions, and
+windows whose batches or rows of hits find no device memory.  Against the in-order scheduler
 (every request scored in full) byte for byte, and against the oracle."""
 import numpy as np
 import pytest
 
 import oracle
-from tests.gpu_util import DeviceWindow, compare_sequential, edge_window, load_window, nb_cap, reqs_of
+from tests.gpu_util import (DeviceWindow, compare_sequential, edge_window, limit_memory, limit_positions, load_window,
+                            nb_cap, reqs_of)
 
 pytestmark = pytest.mark.gpu
 
@@ -134,6 +136,65 @@ def test_batches_mostly_irregular(ps, scorer):
     chains = [([5000 + (j * 7 + r) % 50 for j in range(20)], [10**6 + r]) for r in range(300)]
     sets = [[5000 + j for j in range(10)], [], [5003, 5010, 5017]]
     _check(scorer, edge_window(sets, chains, cap=2000, eta=0.31), "mostly irregular")
+
+
+@pytest.mark.parametrize("max_pos", [1, 130, 1000, 5000])
+@pytest.mark.parametrize("cap", [None, 90])
+def test_batches_cut_by_positions(ps, scorer, max_pos, cap):
+    limit_positions(scorer, max_pos)
+    _check(scorer, _sessions(max_pos, 7, 400, 12, 100, cap=cap), f"{max_pos} positions a batch, cap {cap}")
+
+
+def _limited(ps, scorer, w, room):
+    """The schedule of w with `room` bytes of device memory more than the
+    loaded context holds, against the one without a limit."""
+    dw = DeviceWindow(w)
+    load_window(scorer, w)
+    want = [x.copy() if hasattr(x, "copy") else x for x in dw.schedule(scorer)]
+    state = scorer.state()
+    s = ps.Scorer(0)
+    load_window(s, w)
+    limit_memory(s, 1)
+    with pytest.raises(ps.PackServeError):
+        dw.score(s)  # gives the load's idle buffers back
+    limit_memory(s, limit_memory(s, 0) + room)
+    got = dw.schedule(s)
+    assert (got[0] == want[0]).all() and (got[1] == want[1]).all() and got[2] == want[2]
+    for k, v in s.state().items():
+        assert (v == state[k]).all(), k
+    s.close()
+
+
+def test_schedule_without_room_for_batches(ps, scorer):
+    """The batches' workspace (28 bytes for each of 4 M positions) does not
+    fit: the requests are taken in order, the results are the same."""
+    w = edge_window([[5, 6], [7], [], [8]], None, pool=list(range(1, 20_002)), cap=50_000,
+                    reqs=[(r % 2, 20_000 - r % 7, 0, 0) for r in range(200)], eta=0.31)
+    _limited(ps, scorer, w, 30_000_000)
+
+
+def test_schedule_rows_for_what_batches_leave(ps, scorer):
+    """Chains that end every batch early, on 2,000 instances: what is left to
+    the in-order scheduler needs no more memory than the batches took."""
+    chains = [([5000 + (j * 7 + r) % 50 for j in range(20)], [10**6 + r]) for r in range(3000)]
+    w = edge_window([[5000 + j for j in range(i % 12)] for i in range(2000)], chains, cap=300, eta=0.31)
+    _limited(ps, scorer, w, 12_000_000)
+
+
+def test_schedule_that_runs_out_changes_nothing(ps, scorer):
+    w = _sessions(3, 40, 300, 20, 60)
+    load_window(scorer, w)
+    want = scorer.state()
+    dw = DeviceWindow(w)
+    limit_memory(scorer, 1)
+    with pytest.raises(ps.PackServeError) as e:
+        dw.schedule(scorer)
+    assert e.value.code == ps.binding.PS_E_NOMEM
+    limit_memory(scorer, 0)
+    for k, v in scorer.state().items():
+        assert (v == want[k]).all(), k
+    o = oracle.Oracle.from_window(w)
+    assert (dw.hits(scorer, w.n_inst) == o.window_hits(w)).all()
 
 
 def test_batches_zero_hashes_and_malformed(ps, scorer):
