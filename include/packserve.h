@@ -30,8 +30,8 @@
  *   - A context is not thread-safe; separate contexts are independent.
  *   - Device memory: beside what the snapshot and the calls' tables take, a
  *     context keeps buffers it has used (a replaced snapshot, the temporaries of
- *     a load or commit) for its next call: at most twice the bytes in use, and
- *     4 GiB.  They go back to the device when an allocation of any context of
+ *     a load or commit) for its next call: at most twice the bytes in use (32
+ *     MiB where that is more), and 4 GiB.  They go back to the device when an allocation of any context of
  *     the process on that device fails, and at ps_destroy.
  *   - Block hashes are nonzero 64-bit values (0 is the empty-slot sentinel).
  *     A request's chain is pool[pre_off, pre_off + pre_len) followed by

@@ -147,6 +147,8 @@ struct ps_ctx {
   // per-arrival scheduler: hits of one launch's requests on every instance
   uint32_t* d_seq_hits = nullptr;
   size_t seq_hits_cap = 0;  // bytes
+  SpecRec* d_spec = nullptr;  // a launch's speculative results
+  int32_t spec_cap = 0;       // records
   size_t seq_budget = (size_t)256 << 20;  // bytes of hits per scheduler launch
   // speculative batches (requests per batch; 0: every request scored in full)
   int32_t spec_batch = kSpecBatch;
@@ -452,6 +454,7 @@ ps_status ps_destroy(ps_ctx* c) {
   c->pool.release(c->d_counter);
   for (int k = 0; k < 3; ++k) c->pool.release(c->d_stage[k]);
   c->pool.release(c->d_seq_hits);
+  c->pool.release(c->d_spec);
   c->pool.release(c->d_seq_stats);
   c->pool.release(c->d_gkeys);
   c->pool.release(c->d_grec);
@@ -1357,6 +1360,16 @@ static bool req_ok_host(const ps_req& q, int64_t pool_len) {
          q.tail_len <= pool_len - q.tail_off && (int64_t)q.pre_len + q.tail_len <= PS_MAX_CHAIN;
 }
 
+// Batches of no more requests than this are not worth their 17 launches: 512
+// requests on 16 instances, chains of 130 blocks, take 7.5 ms eight at a time and
+// 17.9 two at a time, where the in-order scheduler, which takes as many per three
+// launches, needs 6.9 and 9.2 ms; sixteen at a time the batches win (4.8 to 6.4).
+// Its insertions grow with the chains: at 2,300 blocks on 64 instances (2,048) it
+// needs 25.2 (34.6) ms two at a time and 16.9 (20.6) eight at a time, the batches
+// 34.3 (38.6) and 13.5 (14.8); four at a time they are even.
+constexpr int32_t kSchedMinBatch = 4, kSchedMinBatchShort = 8;
+constexpr size_t kSchedShortChain = 1024;  // blocks (mean of the window)
+
 // Algorithm 1 per arrival in batches (ps_schedule.hip) of at most `rows`
 // requests, whose hits the context holds; *taken: requests scheduled.  All of
 // them, unless the window's chains share blocks in ways that keep the batches
@@ -1396,13 +1409,14 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
   }
   if (room < longest) return PS_OK;
   const uint32_t max_pos = (uint32_t)std::max(longest, std::min({most, c->max_pos, room}));
+  const uint32_t min_batch = (uint32_t)(mean < kSchedShortChain ? kSchedMinBatchShort : kSchedMinBatch);
+  if (std::min<size_t>(max_n, max_pos / mean) <= min_batch) return PS_OK;
 
   const size_t ws_commit = ps_commit_ws_bytes(kSpecBatch, kSpecBatch, max_pos);
   const size_t words = 32 * (size_t)kSpecBatch;  // the arrays of one word per request
   unsigned char* ws = nullptr;
   PoolScope give{c->pool, ws};
-  const size_t bytes = hits + 256 + kSpecBatch * sizeof(SpecRec) +
-                       (size_t)kSpecBatch * kSpecBatch * sizeof(uint32_t) + words * sizeof(uint32_t) + ws_commit;
+  const size_t bytes = hits + 256 + (size_t)kSpecBatch * kSpecBatch * sizeof(uint32_t) + words * sizeof(uint32_t) + ws_commit;
   {
     const hipError_t e = c->pool.get(&ws, bytes);
     if (e == hipErrorOutOfMemory) return PS_OK;
@@ -1432,7 +1446,7 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
   a.stats = c->d_seq_stats;
   a.hits = c->d_seq_hits;
   a.work = (uint32_t*)take(hits);
-  a.spec = (SpecRec*)take(kSpecBatch * sizeof(SpecRec));
+  a.spec = c->d_spec;
   a.lcp = (uint32_t*)take((size_t)kSpecBatch * kSpecBatch * sizeof(uint32_t));
   uint32_t* w = (uint32_t*)take(words * sizeof(uint32_t));
   auto word_array = [&](uint32_t n) {
@@ -1477,11 +1491,16 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
   HIP_TRY(c, hipMemsetAsync(a.cursor, 0, sizeof(uint32_t), s));
   // Batches are queued as if each took max_n requests; what a batch left
   // out is seen in the cursor, and queued again.  Where little is taken, the
-  // window is left to the in-order scheduler.
+  // window is left to the in-order scheduler: a batch of 256, most of whose
+  // requests were scored in vain, costs 450 to 850 us and 2.6 us a request
+  // taken, the other 15 to 38 us a request.  (A threshold of 24 a batch instead of
+  // 12 to 16 sent a window away whose first batches alone were short: 4.7 -> 10.2
+  // ms for 1,024 requests.)  The first sweep is short, so that a window without
+  // long batches loses little.
   uint32_t done = 0;
-  while (done < (uint32_t)n_req) {
+  for (uint32_t sweep = 16; done < (uint32_t)n_req; sweep = std::min(4 * sweep, 1u << 16)) {
     const uint32_t left = (uint32_t)n_req - done;
-    const uint32_t rounds = (left + max_n - 1) / max_n;
+    const uint32_t rounds = std::min((left + max_n - 1) / max_n, sweep);
     hipError_t e = hipSuccess;
     for (uint32_t k = 0; k < rounds && e == hipSuccess; ++k) {
       e = ps_launch_sched_batch(a, s);
@@ -1493,7 +1512,8 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
     if (e != hipSuccess) return lose_snapshot(c, fail(c, PS_E_DEVICE, "schedule: %s", hipGetErrorString(e)));
     const uint32_t got = now - done;
     done = now;
-    if (got < left && (uint64_t)got * 8 < (uint64_t)rounds * std::min(max_n, 128u)) break;
+    if (got < left && (uint64_t)got < (uint64_t)rounds * (min_batch + max_n / 32)) break;
+    if (got == 0) break;  // (a batch takes one request at least)
   }
   *taken = (int32_t)done;
   return PS_OK;
@@ -1526,8 +1546,14 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
     HIP_TRY(c, c->pool.grow(&c->d_seq_hits, (size_t)rows * row));
     c->seq_hits_cap = (size_t)rows * row;
   }
+  if (spec && rows > c->spec_cap) {
+    c->pool.release(c->d_spec);
+    c->spec_cap = 0;
+    HIP_TRY(c, c->pool.grow(&c->d_spec, (size_t)rows * sizeof(SpecRec)));
+    c->spec_cap = rows;
+  }
   int32_t r_first = 0;
-  if (spec) {
+  if (spec && rows > kSchedMinBatch) {
     const ps_status st =
         run_batches(c, d_pool, pool_len, d_reqs, n_req, (uint32_t)rows, d_out, d_sizes, &r_first, s);
     if (st != PS_OK) return st;
@@ -1551,7 +1577,11 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
     hipError_t e = ps_launch_score(pa, c->hits_in_lds, grid, true, s);
     SeqArgs q{c->t, c->d_inst, c->d_room, c->d_model, d_pool, pool_len, d_reqs, r0, r1, ni,
               c->d_seq_hits, d_forced, d_out, d_sizes, (uint32_t)c->cap, c->d_counter,
-              spec ? c->d_seq_stats : nullptr};
+              spec ? c->d_spec : nullptr, c->d_seq_stats};
+    if (spec && e == hipSuccess)
+      e = ps_launch_spec(SpecArgs{nullptr, (uint32_t)r0, c->d_inst, c->d_model, d_reqs, pool_len, ni, c->d_seq_hits,
+                                  (uint32_t)ni, c->d_spec},
+                         (uint32_t)(r1 - r0), s);
     if (e == hipSuccess) e = ps_launch_seq(q, threads, s);
     if (e != hipSuccess) return lose_snapshot(c, fail(c, PS_E_DEVICE, "schedule: %s", hipGetErrorString(e)));
   }

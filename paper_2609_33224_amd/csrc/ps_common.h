@@ -759,6 +759,18 @@ struct SeqPart {
   uint32_t hroom, nC, nT, wmin, nA, pad;
 };
 
+// Key of the first of the n listed entries whose instance is not marked in
+// `dirty`, or ~0 when there is none (every lane of the wave gets it).  Lane
+// l holds the key of entry l (the lists have at most 64 entries).
+__device__ __forceinline__ uint64_t spec_first_outside(uint64_t k, uint32_t n,
+                                                       const uint64_t* dirty, int lane) {
+  static_assert(kSpecList == 64, "one list entry per lane");
+  const bool out = (uint32_t)lane < n && !test_bit(dirty, (uint32_t)(k & 0xFFFFu));
+  const uint64_t bm = __ballot(out);
+  if (bm == 0ull) return ~0ull;
+  return (uint64_t)lane_value64((int64_t)k, __builtin_ctzll(bm));
+}
+
 // The (r + 1)-th output of a SplitMix64 stream seeded with `seed`
 // (Steele, Lea, Flood; Vigna's public-domain reference).
 __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, int64_t r) {

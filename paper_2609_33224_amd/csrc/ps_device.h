@@ -357,7 +357,8 @@ struct SeqArgs {
   uint32_t* sizes;         // optional |A|,|C|,|T| (Algorithm 1 only)
   uint32_t cap;            // distinct keys allowed per instance
   unsigned long long* dropped;
-  unsigned long long* stats;  // optional: [1] += valid requests scored
+  const SpecRec* spec;        // speculative results of requests [r0, r1) (null: none)
+  unsigned long long* stats;  // with spec: [0] += decisions taken from them, [1] += scored in full
 };
 
 // One batch of the per-arrival scheduler; the kernels read on the device
@@ -407,6 +408,21 @@ struct SchedArgs {
   int32_t* grp_inst;
 };
 
+// Speculative scoring of requests r0 .. (hdr: of a batch, read on the device)
+// against the states and hits given.
+struct SpecArgs {
+  const SchedHdr* hdr;
+  uint32_t r0;
+  const InstState* inst;
+  const DevModel* model;
+  const ps_req* reqs;
+  int64_t pool_len;
+  int32_t n_inst;
+  const uint32_t* hits;
+  uint32_t stride;  // words between two requests' rows of hits
+  SpecRec* out;
+};
+
 struct DeriveArgs {
   const InstState* inst;
   int32_t n, b_max;
@@ -436,8 +452,10 @@ struct BuildArgs {
 // hipMalloc / hipFree cost 78 and 108 us a call here (18 of the 30 ms of a load
 // and four commits on a pool of 64).  Idle buffers are kept up to twice the
 // bytes in use (a reload leaves the old snapshot and the build's temporaries
-// behind, less than twice the new one) and to kPoolIdleMax, the oldest going
-// back to the device beyond that.  put() waits for the device, as hipFree does,
+// behind, less than twice the new one), to kPoolIdleMin on a small pool (a
+// scheduling call's workspace: 480 -> 530 us for 64 requests on 4 instances
+// where it is allocated each time) and to kPoolIdleMax, the oldest going back to
+// the device beyond that.  put() waits for the device, as hipFree does,
 // so no stream still reads a buffer that is handed out again.  grow / release:
 // buffers that stay until they are outgrown, straight from and to the device.
 // An allocation that fails is tried again without the idle buffers of this
@@ -498,7 +516,7 @@ class DevPool {
   std::vector<Block> idle_;
   size_t idle_bytes_ = 0;
 };
-constexpr size_t kPoolIdleMax = (size_t)4 << 30;
+constexpr size_t kPoolIdleMin = (size_t)32 << 20, kPoolIdleMax = (size_t)4 << 30;
 
 }  // namespace ps
 
@@ -560,6 +578,8 @@ hipError_t ps_launch_group(const ps::ScoreArgs& a, int grid, hipStream_t s, hipE
 // Per-arrival scheduler: one workgroup of `threads` (a multiple of 64, at
 // most kSeqMaxThreads) over requests [a.r0, a.r1).
 hipError_t ps_launch_seq(const ps::SeqArgs& a, int threads, hipStream_t s);
+// Speculative results of n requests.
+hipError_t ps_launch_spec(const ps::SpecArgs& a, uint32_t n, hipStream_t s);
 // One batch of the per-arrival scheduler, without its commit.
 hipError_t ps_launch_sched_batch(const ps::SchedArgs& a, hipStream_t s);
 size_t ps_seq_lds_bytes(int32_t n_inst);

@@ -121,7 +121,7 @@ void DevPool::put_idle(void* p) {
     idle_bytes_ += b.bytes;
     break;
   }
-  while (!idle_.empty() && idle_bytes_ > std::min(kPoolIdleMax, 2 * live_bytes_)) {
+  while (!idle_.empty() && idle_bytes_ > std::min(kPoolIdleMax, std::max(kPoolIdleMin, 2 * live_bytes_))) {
     (void)hipFree(idle_.front().p);
     idle_bytes_ -= idle_.front().bytes;
     idle_.erase(idle_.begin());

@@ -37,19 +37,6 @@ constexpr uint32_t kBelow = 2u;    // one that is in A lies below the batch's W_
 constexpr uint32_t kMinThen = 4u;  // one was at W_min ...
 constexpr uint32_t kMinNow = 8u;   // ... and one that is in A is
 
-// Key of the first of the n listed entries whose instance is not marked in
-// `dirty`, or ~0 when there is none (every lane of the wave gets it).  Lane
-// l holds the key of entry l (the lists have at most 64 entries).
-__device__ __forceinline__ uint64_t spec_first_outside(uint64_t k, uint32_t n,
-                                                       const uint64_t* dirty, int lane) {
-  static_assert(kSpecList == 64, "one list entry per lane");
-  const bool out = (uint32_t)lane < n && !test_bit(dirty, (uint32_t)(k & 0xFFFFu));
-  const uint64_t bm = __ballot(out);
-  if (bm == 0ull) return ~0ull;
-  return (uint64_t)lane_value64((int64_t)k, __builtin_ctzll(bm));
-}
-
-
 // ------------------------------------------------------------------- a batch
 // The next batch: requests from the cursor on, at most max_n of them and (but
 // for a single longer one) at most max_pos positions.
@@ -278,7 +265,8 @@ struct SpecShared {
                                           // of its members ran out (read in the next round)
 };
 
-// One workgroup per request of a batch: Algorithm 1's sets against the
+// One workgroup per request of a batch (or of a launch of the in-order
+// scheduler): Algorithm 1's sets against the
 // state at the batch's start (hits from the batch's hits pass), exactly as
 // the scheduler evaluates them (same device functions, same fp32 values),
 // without a decision: |A|, |C|, |T|, W_min and the first kSpecList members
@@ -288,14 +276,18 @@ struct SpecShared {
 // thread that saw more members than it kept (its next member is unknown),
 // so every list is the exact start of the ordered set.  Keyed selectors
 // only (not Random, not H-C-Q).
-__global__ __launch_bounds__(kSeqMaxThreads) void spec_kernel(SchedArgs a) {
+__global__ __launch_bounds__(kSeqMaxThreads) void spec_kernel(SpecArgs a) {
   __shared__ SpecShared sh;
-  const SchedHdr h = *a.hdr;
-  if (blockIdx.x >= h.n) return;
+  uint32_t r0 = a.r0;
+  if (a.hdr) {
+    const SchedHdr h = *a.hdr;
+    if (blockIdx.x >= h.n) return;
+    r0 = h.r0;
+  }
   const int tid = threadIdx.x, NT = blockDim.x;
   const int lane = tid & 63, wv = tid >> 6, nwv = NT >> 6;
   const int32_t n_inst = a.n_inst;
-  const int32_t r = (int32_t)(h.r0 + blockIdx.x);
+  const int32_t r = (int32_t)(r0 + blockIdx.x);
   const ps_req q = a.reqs[r];
   if (!req_valid(q, a.pool_len)) return;  // the scheduler rejects it without a look here
   const DevModel& m = *a.model;
@@ -304,8 +296,8 @@ __global__ __launch_bounds__(kSeqMaxThreads) void spec_kernel(SchedArgs a) {
   const float Z = recompute_raw(m, Lf, Lf);
   const float slo = fmaxf(m.ttft_floor, t_prefill(m, Lf, 0.0f));
   const bool kvc = !(m.flags & PS_F_NO_KVC_FILTER) && Z > 0.0f;
-  const uint32_t* H = a.hits + (size_t)blockIdx.x * sched_row_stride(n_inst);
-  SpecRec* o = a.spec + blockIdx.x;
+  const uint32_t* H = a.hits + (size_t)blockIdx.x * a.stride;
+  SpecRec* o = a.out + blockIdx.x;
 
   // |A| and W_min
   uint32_t al = 0, wl = 0x7F800000u;
@@ -1012,6 +1004,12 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(SchedArgs a) {
 
 }  // namespace
 
+hipError_t ps_launch_spec(const SpecArgs& a, uint32_t n, hipStream_t s) {
+  if (n == 0u) return hipSuccess;
+  hipLaunchKernelGGL(spec_kernel, dim3(n), dim3(kSeqMaxThreads), 0, s, a);
+  return hipGetLastError();
+}
+
 size_t ps_sched_lds_bytes(int32_t n_inst) {
   return sizeof(SchedShared) + ((size_t)n_inst + 127) / 128 * 2 * sizeof(uint64_t) +
          (n_inst <= kSchedRowMax ? 2 * (size_t)sched_row_stride(n_inst) * sizeof(uint32_t) : 0);
@@ -1023,7 +1021,9 @@ hipError_t ps_launch_sched_batch(const SchedArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kSpecBatch), 0, s, a);
   hipLaunchKernelGGL(first_kernel, dim3(n, std::min(((unsigned)a.n_inst + 255u) / 256u, 256u)), dim3(256), 0, s, a);
   hipLaunchKernelGGL(walk_kernel, dim3(4096), dim3(64), 0, s, a);
-  hipLaunchKernelGGL(spec_kernel, dim3(n), dim3(kSeqMaxThreads), 0, s, a);
+  const SpecArgs sa{a.hdr, 0u, a.inst, a.model, a.reqs, a.pool_len, a.n_inst, a.hits, sched_row_stride(a.n_inst),
+                    a.spec};
+  hipLaunchKernelGGL(spec_kernel, dim3(n), dim3(kSeqMaxThreads), 0, s, sa);
   hipLaunchKernelGGL(intern_clear_kernel, dim3(pgrid), dim3(256), 0, s, a);
   hipLaunchKernelGGL(intern_kernel, dim3(pgrid), dim3(256), 0, s, a);
   hipLaunchKernelGGL(check_kernel, dim3(pgrid), dim3(256), 0, s, a);

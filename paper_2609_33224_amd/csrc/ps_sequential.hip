@@ -7,16 +7,33 @@
 namespace {
 
 // ----------------------------------------------------- per-arrival scheduler
+// One wave's share of the check of a speculative result (below).
+struct FastPart {
+  uint64_t keyT, keyF;  // least selector / fallback key over the changed instances in T / C
+  uint32_t conf;        // a changed instance now holds the block where the hit stopped
+  uint32_t wb, wc;      // least W over the changed instances eligible then / now
+  uint32_t eb, ec;      // changed instances eligible then / now
+  uint32_t cb, cc;      // ... in C then / now
+  uint32_t tb, tc;      // ... in T then / now
+  uint32_t pad;
+};
+
 // Workgroup LDS of the scheduler (a fixed layout, plus the dirty bitmap).
 struct SeqShared {
   uint64_t stage[kSeqStage];          // the request's chain head
   SeqPart part[2][kSeqWaves];         // reduction partials (alternating)
+  FastPart fp[kSeqWaves];
   uint32_t cnt[kSeqU][kSeqWaves];     // per-wave counts of one insert step
   uint32_t ext[kExtMax][2];           // hit extensions: instance, first unknown position
   uint32_t ring[3];                   // first-absent minima of the sweeps
   uint32_t n_ext, hit, pick, count;
   int64_t rp;                         // row position found by a run walk's probe
-  uint32_t n_scored;                  // valid requests taken
+  // instances placed on in this launch (the dirty ones), in order, with
+  // their state at the launch's start
+  uint32_t n_u;
+  uint32_t n_fast, n_full;            // decisions from speculation / scored in full
+  uint32_t u_id[kSpecBatch];
+  InstState u_old[kSpecBatch];
 };
 
 __device__ __forceinline__ uint64_t seq_key(const SeqShared& sh, const ChainRef& c, int32_t j) {
@@ -188,7 +205,11 @@ __device__ uint32_t seq_run_walk(const Tables& t, uint32_t i, const ChainRef& c,
 //      blocks past the cap).
 // The next request starts after a workgroup barrier, so its probes see
 // those inserts.  Replay (a.forced): the given instance is
-// measured and committed, without (1) and (3).
+// measured and committed, without (1) and (3).  SPEC: requests were scored
+// against the launch's start (a.spec, keyed selectors only); (1) to (3) run only
+// where that does not settle the decision.  A template, so that the other calls
+// do not carry its registers: 15 against 16 us a decision on 16 instances.
+template <bool SPEC>
 __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   SeqShared& sh = *reinterpret_cast<SeqShared*>(smem);
@@ -204,7 +225,7 @@ __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
   ScoreArgs sa{};
   sa.inst = a.inst;
   for (int32_t w = tid; w < nw; w += NT) dirty[w] = 0ull;
-  if (tid == 0) sh.n_scored = 0u;
+  if (tid == 0) sh.n_u = sh.n_fast = sh.n_full = 0u;
   unsigned long long drop = 0;
   int pb = 0;  // partial buffer of the next reduction (alternates)
   ps_req qn = a.reqs[a.r0];
@@ -227,7 +248,6 @@ __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
       }
       continue;
     }
-    if (tid == 0) sh.n_scored += 1u;
     const ChainRef c{a.pool + q.pre_off, a.pool + q.tail_off, q.pre_len, q.pre_len + q.tail_len};
     const int32_t ell = c.len;
     const ReqLen L{(int64_t)ell * m.bs, ell};
@@ -241,6 +261,135 @@ __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
     const float tpf_cold = t_prefill(m, Lf, 0.0f);
     const float slo = fmaxf(m.ttft_floor, tpf_cold);
     const bool kvc = !(m.flags & PS_F_NO_KVC_FILTER) && Z > 0.0f;
+    bool staged = false, fast = false;
+
+    // (0) the speculative result: scored against the launch's starting
+    // state, it still decides the request unless an instance placed on
+    // since then (the set U) changes W_min or the choice
+    if (SPEC) {
+      const SpecRec& sp = a.spec[r - a.r0];
+      stage_chain(sh, c, tid, NT);  // the commit reads it
+      const uint64_t lt_key = sp.lt[lane];  // read before n is known
+      staged = true;
+      const uint32_t n_u = sh.n_u;
+      const uint32_t wmin_b = sp.wmin;
+      const float wmin = __uint_as_float(wmin_b);
+      FastPart f{~0ull, ~0ull, 0u, ~0u, ~0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+      for (uint32_t k = (uint32_t)tid; k < n_u; k += (uint32_t)NT) {
+        const uint32_t u = sh.u_id[k];
+        const InstState so = sh.u_old[k];  // as the speculative scoring saw it
+        const InstState sc = a.inst[u];    // now
+        const uint32_t h = H[u];           // its hit then
+        const bool eb = eligible(m, so.A1, so.S, L), ec = eligible(m, sc.A1, sc.S, L);
+        // the hit still stops at h unless u has taken the block at h since
+        if (ec && (int32_t)h < ell && probe(a.t, u, chain_global(c, (int32_t)h))) f.conf = 1u;
+        const uint32_t wb = __float_as_uint(fmaxf(0.0f, recompute_raw(m, blocks_f(m, L.blocks - (int32_t)h), Lf)));
+        const bool cpass = !kvc || (__uint_as_float(wb) - wmin) / Z <= m.eta;
+        if (eb) {
+          f.eb += 1u;
+          f.wb = wb < f.wb ? wb : f.wb;
+          if (cpass) {
+            f.cb += 1u;
+            if (a.sizes)
+              f.tb += member_with(m, [&]() { return so; }, h, L, Lf, wmin, Z, kvc, slo).inT ? 1u : 0u;
+          }
+        }
+        if (ec) {
+          f.ec += 1u;
+          f.wc = wb < f.wc ? wb : f.wc;
+          const Member mb = member_with(m, [&]() { return sc; }, h, L, Lf, wmin, Z, kvc, slo);
+          if (mb.inC) {
+            f.cc += 1u;
+            const uint64_t lm = (uint64_t)(mb.st.P + mb.n_tok) * (uint64_t)mb.st.A1;
+            const uint64_t kf = (m.flags & PS_F_FALLBACK_DCQ) ? dcq_key(mb.st, h, u) : ((lm << 16) | u);
+            f.keyF = kf < f.keyF ? kf : f.keyF;
+            if (mb.inT) {
+              f.tc += 1u;
+              const uint64_t kt = select_key(m.sel, mb.st, h, u, lm);
+              f.keyT = kt < f.keyT ? kt : f.keyT;
+            }
+          }
+        }
+      }
+      {
+        FastPart w;
+        w.keyT = wave_min_u64(f.keyT);
+        w.keyF = wave_min_u64(f.keyF);
+        w.conf = __ballot(f.conf != 0u) ? 1u : 0u;
+        w.wb = wave_min_u32(f.wb);
+        w.wc = wave_min_u32(f.wc);
+        w.eb = wave_sum_u32(f.eb);
+        w.ec = wave_sum_u32(f.ec);
+        w.cb = wave_sum_u32(f.cb);
+        w.cc = wave_sum_u32(f.cc);
+        w.tb = wave_sum_u32(f.tb);
+        w.tc = wave_sum_u32(f.tc);
+        w.pad = 0u;
+        if (lane == 0) sh.fp[wv] = w;
+      }
+      __syncthreads();
+      FastPart g = sh.fp[0];
+      for (int k = 1; k < nwv; ++k) {
+        const FastPart& p = sh.fp[k];
+        g.keyT = p.keyT < g.keyT ? p.keyT : g.keyT;
+        g.keyF = p.keyF < g.keyF ? p.keyF : g.keyF;
+        g.conf |= p.conf;
+        g.wb = p.wb < g.wb ? p.wb : g.wb;
+        g.wc = p.wc < g.wc ? p.wc : g.wc;
+        g.eb += p.eb;
+        g.ec += p.ec;
+        g.cb += p.cb;
+        g.cc += p.cc;
+        g.tb += p.tb;
+        g.tc += p.tc;
+      }
+      const uint32_t nA_now = sp.nA - g.eb + g.ec;
+      // W_min is unchanged unless a hit moved (conf) or the only changed
+      // instances at the minimum all left A: then it is not known here
+      bool ok = g.conf == 0u && !(g.wb == wmin_b && g.wc != wmin_b) && g.wc >= wmin_b;
+      if (ok && nA_now > 0u) {
+        // the other members of T and C are as speculated; the first listed
+        // one outside U is the least of them when the list shows it
+        const uint64_t t0 = spec_first_outside(lt_key, sp.nLT, dirty, lane);
+        if (t0 == ~0ull && sp.nLT < sp.nT) {
+          ok = false;
+        } else {
+          const uint64_t kT = t0 < g.keyT ? t0 : g.keyT;
+          if (kT != ~0ull) {
+            best = (int32_t)(kT & 0xFFFFu);
+            fl = 0;
+          } else {
+            const uint64_t f0 = spec_first_outside(sp.lf[lane], sp.nLF, dirty, lane);
+            if (f0 == ~0ull && sp.nLF < sp.nC) {
+              ok = false;
+            } else {
+              const uint64_t kF = f0 < g.keyF ? f0 : g.keyF;
+              if (kF != ~0ull) {
+                best = (int32_t)(kF & 0xFFFFu);
+                fl = PS_R_FALLBACK;
+              }
+            }
+          }
+        }
+      }
+      if (ok) {
+        fast = true;
+        nA = nA_now;
+        if (nA_now > 0u) {
+          nC = sp.nC - g.cb + g.cc;
+          nT = sp.nT - g.tb + g.tc;
+        }
+      } else {
+        best = -1;
+        fl = PS_R_REJECT;
+      }
+      if (tid == 0) {
+        if (fast) sh.n_fast += 1u;
+        else sh.n_full += 1u;
+      }
+    }
+
+    if (!fast) {
     // (1) capacity guard
     if (!replay && L <= room_ub) {
       uint32_t al = 0;
@@ -279,7 +428,7 @@ __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
     const bool work = replay ? forced >= 0 : nA > 0;
     if (work) {
       // (2) live hits
-      stage_chain(sh, c, tid, NT);
+      if (!staged) stage_chain(sh, c, tid, NT);
       if (tid == 0) sh.n_ext = 0u;
       __syncthreads();
       for (int32_t base = 0; base < n_inst; base += kSeqB * NT) {
@@ -487,12 +636,18 @@ __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
         }
       }
     }
+    }  // !fast
 
     // (4) result and commit
     if (best >= 0 && best % NT == tid) {
       const uint32_t v = H[best];
       const int64_t c_tok = (int64_t)v * m.bs;
       InstState st = a.inst[best];
+      if (SPEC && !test_bit(dirty, (uint32_t)best) && sh.n_u < (uint32_t)kSpecBatch) {
+        sh.u_id[sh.n_u] = (uint32_t)best;  // first placement on it in this launch
+        sh.u_old[sh.n_u] = st;
+        sh.n_u += 1u;
+      }
       const Lat lt = latency(m, st, blocks_f(m, L.blocks - (int32_t)v), blocks_f(m, (int32_t)v), L);
       if (lt.ttft > slo) fl |= PS_R_TTFT_MISS;
       a.out[r] = ps_result{best, (int32_t)v, lt.ttft, lt.tpot, fl};
@@ -680,7 +835,10 @@ __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
     }
   }
   if (tid == 0 && drop) atomicAdd(a.dropped, drop);
-  if (tid == 0 && a.stats && sh.n_scored) atomicAdd(a.stats + 1, (unsigned long long)sh.n_scored);
+  if (SPEC && tid == 0) {
+    atomicAdd(a.stats, (unsigned long long)sh.n_fast);
+    atomicAdd(a.stats + 1, (unsigned long long)sh.n_full);
+  }
 }
 
 }  // namespace
@@ -693,6 +851,9 @@ size_t ps_seq_lds_bytes(int32_t n_inst) {
 hipError_t ps_launch_seq(const SeqArgs& a, int threads, hipStream_t s) {
   if (a.r1 <= a.r0) return hipSuccess;
   if (threads < 64 || threads > kSeqMaxThreads || threads % 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(seq_kernel, dim3(1), dim3(threads), ps_seq_lds_bytes(a.n_inst), s, a);
+  if (a.spec)
+    hipLaunchKernelGGL(seq_kernel<true>, dim3(1), dim3(threads), ps_seq_lds_bytes(a.n_inst), s, a);
+  else
+    hipLaunchKernelGGL(seq_kernel<false>, dim3(1), dim3(threads), ps_seq_lds_bytes(a.n_inst), s, a);
   return hipGetLastError();
 }

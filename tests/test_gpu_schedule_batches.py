@@ -138,6 +138,22 @@ def test_batches_mostly_irregular(ps, scorer):
     _check(scorer, edge_window(sets, chains, cap=2000, eta=0.31), "mostly irregular")
 
 
+@pytest.mark.parametrize("cap", [9000, 130])
+def test_what_batches_leave_is_speculated(ps, scorer, cap):
+    """Every chain begins somewhere else in one session, so any two of them end
+    a batch: the in-order scheduler takes the window, from speculative results
+    too (a launch of up to 256 requests scored in parallel)."""
+    rng = np.random.default_rng(11)
+    base = [1000 + j for j in range(120)]
+    chains = []
+    for r in range(500):
+        k = int(rng.integers(0, 60))
+        chains.append((base[k:k + 60], [10**6 + 10 * r + j for j in range(int(rng.integers(0, 3)))]))
+    sets = [base[:int(rng.integers(0, 120))] for _ in range(64)]
+    b = _check(scorer, edge_window(sets, chains, cap=cap, eta=0.31), f"one session, cap {cap}")
+    assert b[4][0] > 100, f"decided from speculation: {b[4]}"
+
+
 @pytest.mark.parametrize("max_pos", [1, 130, 1000, 5000])
 @pytest.mark.parametrize("cap", [None, 90])
 def test_batches_cut_by_positions(ps, scorer, max_pos, cap):
