@@ -155,6 +155,31 @@ def test_zero_hash_refused(ps, scorer, at):
     compare_decisions(res, None, oracle.Oracle.from_window(w).window_score(w))
 
 
+@pytest.mark.parametrize("n", [300, 65536, 65537, 70001])  # the calling thread looks up to 65,536
+def test_zero_hash_comes_first(ps, scorer, n):
+    """A zero hash is refused as such whatever else is wrong with the call,
+    also where nothing is placed, and a good call goes through."""
+    w = edge_window([[5, 6, 7], [8]], [list(range(10, 10 + n))], cap=2 * n)
+    load_window(scorer, w)
+    reqs = reqs_of(w)
+    for at in (0, n // 2, n - 1):
+        pool = w.pool.copy()
+        pool[at] = 0
+        for call in (lambda: scorer.score(pool, reqs),
+                     lambda: scorer.commit(pool, reqs, np.array([1], np.int32)),
+                     lambda: scorer.commit(pool, reqs, np.array([-1], np.int32)),
+                     lambda: scorer.commit(pool, reqs, np.array([2], np.int32))):
+            with pytest.raises(ps.PackServeError, match=rf"zero block hash at pool\[{at}\]") as e:
+                call()
+            assert e.value.code == ps.binding.PS_E_INVAL
+    with pytest.raises(ps.PackServeError) as e:
+        scorer.commit(w.pool, reqs, np.array([2], np.int32))
+    assert e.value.code == ps.binding.PS_E_RANGE
+    assert scorer.commit(w.pool, reqs, np.array([-1], np.int32)) == 0
+    compare_decisions(scorer.score(w.pool, reqs), None, oracle.Oracle.from_window(w).window_score(w))
+    _check(scorer, w, np.array([1], np.int32), f"pool of {n}")
+
+
 @pytest.mark.parametrize("max_pos", [1, 100, 1024, 3000])
 @pytest.mark.parametrize("cap", [None, 41, 300])
 def test_commit_slices(ps, scorer, max_pos, cap):
