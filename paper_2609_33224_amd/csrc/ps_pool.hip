@@ -47,9 +47,10 @@ size_t DevPool::held() {
 // Room for one more entry in both lists (nothing is thrown across the ABI).
 bool DevPool::reserve_live() {
   try {
-    live_.reserve(live_.size() + 1);
+    if (live_.size() == live_.capacity()) live_.reserve(2 * live_.size() + 32);
     std::lock_guard<std::mutex> lk(mu_);
-    idle_.reserve(live_.size() + 1 + idle_.size());
+    const size_t need = live_.size() + 1 + idle_.size();
+    if (need > idle_.capacity()) idle_.reserve(2 * need);
   } catch (const std::exception&) {
     return false;
   }
