@@ -393,6 +393,7 @@ ps_status refresh_derived(ps_ctx* c) {
     st.A1 = st.D + st.Q + 1;
     st.seg = segment_of_dev(c->h_model, st.A1);
   }
+  HIP_TRY(c, hipGetLastError());  // an earlier call's error must not end this one half way
   HIP_TRY(c, hipMemcpy(c->d_inst, c->h_state.data(), c->h_state.size() * sizeof(InstState),
                        hipMemcpyHostToDevice));
   HIP_TRY(c, ps_launch_derive(derive_args(*c, c->n_inst, c->h_model), c->stream));
@@ -401,6 +402,7 @@ ps_status refresh_derived(ps_ctx* c) {
 
 ps_status upload_model(ps_ctx* c) {
   c->h_model.mono = monotone(c->h_model);
+  HIP_TRY(c, hipGetLastError());  // (as above)
   HIP_TRY(c, hipMemcpy(c->d_model, &c->h_model, sizeof c->h_model, hipMemcpyHostToDevice));
   return refresh_lmax(c);
 }
@@ -1379,6 +1381,7 @@ ps_status ps_commit(ps_ctx* c, const uint64_t* pool, int64_t pool_len, const ps_
   HIP_TRY(c, hipMemcpyAsync(dr, reqs, (size_t)n * sizeof(ps_req), hipMemcpyHostToDevice, s));
   HIP_TRY(c, hipMemcpyAsync(d_up, upload.data(), upload.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
   HIP_TRY(c, hipMemsetAsync(c->d_counter, 0, sizeof(unsigned long long), s));
+  HIP_TRY(c, hipGetLastError());  // an earlier call's error must not end this one half way
   for (const CommitSlice& sl : slices) {
     const hipError_t e =
         launch_slice(c, sl, (const uint32_t*)d_up, ws, (const uint64_t*)dp, (const ps_req*)dr, s);
@@ -1561,6 +1564,7 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
                                 ps_result* d_out, uint32_t* d_sizes, int64_t* n_dropped,
                                 hipStream_t s) {
   const int32_t ni = c->n_inst;
+  HIP_TRY(c, hipGetLastError());  // an earlier call's error must not end this one half way
   HIP_TRY(c, hipMemsetAsync(c->d_counter, 0, sizeof(unsigned long long), s));
   if (!c->d_seq_stats) HIP_TRY(c, c->pool.grow(&c->d_seq_stats, 2 * sizeof(unsigned long long)));
   HIP_TRY(c, hipMemsetAsync(c->d_seq_stats, 0, 2 * sizeof(unsigned long long), s));

@@ -80,6 +80,13 @@ def limit_positions(scorer, n):
     assert f(scorer.ctx, int(n)) == 0
 
 
+def leave_error():
+    """A HIP call of the program that failed (no such device), its error not
+    read."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    assert ctypes.CDLL(path).hipSetDevice(1 << 20) != 0
+
+
 class DeviceWindow:
     """The window's pool and descriptors resident on the GPU."""
 

@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import synth
-from tests.gpu_util import DeviceWindow, compare_decisions, limit_memory, load_window
+from tests.gpu_util import DeviceWindow, compare_decisions, leave_error, limit_memory, load_window, reqs_of
 
 pytestmark = pytest.mark.gpu
 
@@ -129,3 +129,31 @@ def test_idle_memory_of_another_context(ps, scorer):
     res, sizes = DeviceWindow(w).score(other)
     compare_decisions(res, sizes, oracle.Oracle.from_window(w).window_score(w))
     other.close()
+
+
+@pytest.mark.parametrize("what", ["commit", "schedule", "replay", "events", "feedback"])
+def test_an_earlier_error_does_not_end_a_call_half_way(ps, scorer, what):
+    """A failed HIP call of the program itself, whose error nobody read: a call
+    that changes the snapshot reports it before any change, or works."""
+    w = _window(9)
+    dw = DeviceWindow(w)
+    inst = (np.arange(w.n_req) % w.n_inst).astype(np.int32)
+    every = np.arange(w.n_inst)
+    call = {"commit": lambda: scorer.commit(w.pool, reqs_of(w), inst), "schedule": lambda: dw.schedule(scorer),
+            "replay": lambda: dw.replay(scorer, inst),
+            "events": lambda: scorer.apply_events(every, 0 * every + ps.PS_EV_DECODE_TOKENS, 100_000 + 0 * every),
+            "feedback": lambda: scorer.feedback_decode([4] * 50, [1000] * 50, [0.5] * 50)}[what]
+
+    def seen():
+        res, sizes = dw.score(scorer)
+        return [*scorer.state().values(), *scorer.model().values(), dw.hits(scorer, w.n_inst), sizes.copy(), res.copy()]
+
+    load_window(scorer, w)
+    want = seen()
+    leave_error()
+    try:
+        call()
+    except ps.PackServeError:
+        assert all((a == b).all() if hasattr(a, "all") else a == b for a, b in zip(want, seen()))
+        call()
+    assert not (want[-1] == seen()[-1]).all()  # the call had its effect
