@@ -1168,11 +1168,12 @@ static ps_status lose_snapshot(ps_ctx* c, ps_status st) {
   return st;
 }
 
-// Gives a pool buffer back at the end of the scope.
+// Gives a pool buffer back at the end of the scope (its stream was waited for
+// there, or the snapshot lost, which waits for the device).
 struct PoolScope {
   DevPool& pool;
   unsigned char*& p;
-  ~PoolScope() { pool.put(p); }
+  ~PoolScope() { pool.put_done(p); }
 };
 
 // After placements were committed on the device (work queued on `s`, the
@@ -1189,7 +1190,7 @@ static ps_status refresh_committed(ps_ctx* c, hipStream_t s, unsigned char*& ws,
   HIP_TRY(c, hipMemcpyAsync(c->h_count.data(), c->t.count, c->h_count.size() * sizeof(uint32_t),
                             hipMemcpyDeviceToHost, s));
   HIP_TRY(c, hipStreamSynchronize(s));
-  c->pool.put(ws);
+  c->pool.put_done(ws);
   HIP_TRY(c, ps_build_index(c->t, c->n_inst, c->h_count.data(), &c->x, &c->pool, s));
   HIP_TRY(c, hipStreamSynchronize(s));
   const ps_status lst = refresh_lmax(c);

@@ -483,6 +483,13 @@ class DevPool {
     (put_idle((void*)p), ...);
     ((p = nullptr), ...);
   }
+  // One buffer whose last use the caller has waited for (a device wait more a
+  // call: 5.89 -> 5.98 ms for a load and four commits on a pool of 64).
+  template <class T>
+  void put_done(T*& p) {
+    put_idle((void*)p);
+    p = nullptr;
+  }
   template <class T>
   hipError_t grow(T** out, size_t bytes) {
     return device_alloc((void**)out, bytes);
