@@ -19,10 +19,12 @@
 //   * the first occurrences, counted in order, are the row positions of the
 //     new blocks, and the cap refuses exactly those whose rank reaches the
 //     room left.
-// Kernels: probe (table lookups, scratch set), mark (hits, first occurrences
-// counted per chunk), groups (ranks at the group bounds), insert (table,
-// row), drop (refused positions, where a cap binds) and state.  All are bound by random 64-byte reads and memory-side atomics, so each thread
-// keeps kCommitU positions in flight.
+// Kernels: clear (scratch set), probe (table lookups, scratch set), mark (hits,
+// first occurrences counted per chunk), scan (those counts), group (ranks at the
+// group bounds), insert (table, row), drop (refused positions, where a cap
+// binds) and state (counters; the scheduler's batches move them themselves).
+// All but scan and group are bound by random 64-byte reads and memory-side
+// atomics, so each thread keeps kCommitU positions in flight.
 
 #include "ps_common.h"
 

@@ -191,7 +191,8 @@ __device__ __forceinline__ IdxHit index_lookup(const GIndex& x, uint64_t key, bo
   return h;
 }
 
-// Single-lane lookup (commit path only).
+// A whole bucket read by one lane (64 bytes, four loads): the commit, the
+// exhaustive probe, the scheduler's first-block pass.
 __device__ __forceinline__ Bucket load_bucket(const uint64_t* p) {
   const ulonglong2* q = reinterpret_cast<const ulonglong2*>(p);
   const ulonglong2 a = q[0], b = q[1], c = q[2], d = q[3];
@@ -596,18 +597,6 @@ __device__ __forceinline__ Lat latency(const M& m, const InstState& st, float n,
   Lat r;
   r.tpot = t_iter + interf;
   r.ttft = tp + m.a[0] * (float)st.Q + m.a[1] * tok_f(st.P);
-  return r;
-}
-
-// Another lane's state (every lane must call it).
-__device__ __forceinline__ InstState shfl_state(const InstState& st, int src) {
-  InstState r;
-  r.D = __shfl(st.D, src);
-  r.Q = __shfl(st.Q, src);
-  r.A1 = __shfl(st.A1, src);
-  r.seg = __shfl(st.seg, src);
-  r.P = __shfl(st.P, src);
-  r.S = __shfl(st.S, src);
   return r;
 }
 

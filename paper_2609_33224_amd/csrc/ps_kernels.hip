@@ -403,7 +403,7 @@ __device__ __forceinline__ void index_walk(const ScoreArgs& a, const ChainRef& c
     // batches (a session's blocks on the instances its requests went to):
     // each along its own row below, hundreds of positions per step, where the
     // index takes two dependent reads for eight positions.  2,048 blocks on
-    // two to four live holders: 1.17 -> 0.09 ms for the popular pass of 1,500
+    // two to four live holders: 1.17 -> 0.05 ms for the popular pass of 1,500
     // requests on 1,024 instances.  (Holders of a shared prompt leave at its
     // end, within a batch; rows would then cost each of them a probe.)
     if (nalive == 1 || (nalive <= kFewLive && calm >= 2)) break;

@@ -112,9 +112,10 @@ __global__ __launch_bounds__(256) void first_kernel(SchedArgs a) {
   }
 }
 
-// A wave per instance found, along its row, 512 positions per step (17 us for
-// 256 requests with about one holder each; walking all of a request's holders
-// in one wave by table probes took 73 us).
+// A wave per instance found, along its row, 256 positions in a run's first step
+// and 512 after it (17 us for 256 requests with about one holder
+// each; walking all of a request's holders in one wave by table probes took 73
+// us).
 __global__ __launch_bounds__(64) void walk_kernel(SchedArgs a) {
   const uint32_t n = *a.n_work;
   const uint32_t r0 = a.hdr->r0;
@@ -508,7 +509,7 @@ static_assert(sizeof(SchedShared) + kSchedRowMax / 8 + 2 * 4 * kSchedRowMax <= 6
 // memory, and what bounds it is the deciding waves' own instruction issue (one
 // wave, four cycles an instruction) and LDS latency: hence the model in scalar
 // registers, ballots instead of reductions, and counts only where asked for.
-// 256 decisions on 2,048 instances 658 us, 2.6 us each; with four waves doing
+// 256 decisions on 2,048 instances 656 us, 2.6 us each; with four waves doing
 // all of it and three barriers 3.6 us, with memory-waiting barriers and
 // generic reductions 4.2 us.
 // When a changed instance's hit moved, W_min changed or a list ran out, the

@@ -208,7 +208,7 @@ __device__ uint32_t seq_run_walk(const Tables& t, uint32_t i, const ChainRef& c,
 // measured and committed, without (1) and (3).  SPEC: requests were scored
 // against the launch's start (a.spec, keyed selectors only); (1) to (3) run only
 // where that does not settle the decision.  A template, so that the other calls
-// do not carry its registers: 15 against 16 us a decision on 16 instances.
+// do not carry its registers.
 template <bool SPEC>
 __global__ __launch_bounds__(kSeqMaxThreads) void seq_kernel(SeqArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
