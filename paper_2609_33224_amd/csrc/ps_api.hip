@@ -463,7 +463,6 @@ ps_status ps_destroy(ps_ctx* c) {
   DeviceScope ds(c->device);
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   if (c->aux) (void)hipStreamSynchronize(c->aux);
-  free_snapshot(c);
   c->pool.release(c->d_model);
   c->pool.release(c->d_counter);
   for (int k = 0; k < 3; ++k) c->pool.release(c->d_stage[k]);
@@ -482,6 +481,11 @@ ps_status ps_destroy(ps_ctx* c) {
   c->pool.release(c->d_gpre);
   c->pool.release(c->d_obins);
   c->pool.release(c->d_order);
+  // The tables before the snapshot, whose buffers go back as the bytes in use
+  // shrink: in the other order the next context's first scoring call, which
+  // takes 128 MiB, took 500 us instead of 260 in every third context on a pool
+  // of 256 instances.
+  free_snapshot(c);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   if (c->stream) (void)hipStreamDestroy(c->stream);
   if (c->aux) (void)hipStreamDestroy(c->aux);
@@ -1400,9 +1404,10 @@ static bool req_ok_host(const ps_req& q, int64_t pool_len) {
 // Batches of no more requests than this are not worth their 17 launches: 512
 // requests on 16 instances, chains of 130 blocks, take 7.5 ms eight at a time and
 // 17.9 two at a time, where the in-order scheduler, which takes as many per three
-// launches, needs 6.9 and 9.2 ms; sixteen at a time the batches win (4.8 to 6.4).
+// launches, needs 7.0 and 9.4 ms; sixteen at a time the batches win (4.8; in order 6.4 even
+// with 32).
 // Its insertions grow with the chains: at 2,300 blocks on 64 instances (2,048) it
-// needs 25.2 (34.6) ms two at a time and 16.9 (20.6) eight at a time, the batches
+// needs 25.2 (34.7) ms two at a time and 16.9 (20.6) eight at a time, the batches
 // 34.3 (38.6) and 13.5 (14.8); four at a time they are even.
 constexpr int32_t kSchedMinBatch = 4, kSchedMinBatchShort = 8;
 constexpr size_t kSchedShortChain = 1024;  // blocks (mean of the window)
