@@ -131,6 +131,51 @@ def test_idle_memory_of_another_context(ps, scorer):
     other.close()
 
 
+def test_contexts_in_threads_share_what_lies_idle(ps):
+    """One context runs out again and again, which takes back what the other,
+    in another thread, has just put aside: that one's loads, commits and windows
+    stay the same."""
+    import threading
+    w = _window(10, cap=60000)
+    inst = (np.arange(w.n_req) % w.n_inst).astype(np.int32)
+    dw, poor_dw = DeviceWindow(w), DeviceWindow(w)
+    o = oracle.Oracle.from_window(w)
+    before = o.window_score(w)
+    o.commit(w.pool, w.pre_off, w.pre_len, w.tail_off, w.tail_len, inst)
+    after = o.window_score(w)
+    done, failures = threading.Event(), []
+
+    def run_out():
+        s = ps.Scorer(0)
+        load_window(s, w)
+        limit_memory(s, 1)
+        while not done.is_set():
+            try:
+                poor_dw.score(s)
+                failures.append("the call got memory")
+                break
+            except ps.PackServeError as e:
+                if e.code != ps.binding.PS_E_NOMEM:
+                    failures.append(str(e))
+                    break
+        s.close()
+
+    t = threading.Thread(target=run_out)
+    t.start()
+    try:
+        rich = ps.Scorer(0)
+        for _ in range(12):
+            load_window(rich, w)
+            compare_decisions(*dw.score(rich), before)
+            rich.commit(w.pool, reqs_of(w), inst)
+            compare_decisions(*dw.score(rich), after)
+        rich.close()
+    finally:
+        done.set()
+        t.join()
+    assert not failures, failures
+
+
 @pytest.mark.parametrize("what", ["commit", "schedule", "replay", "events", "feedback"])
 def test_an_earlier_error_does_not_end_a_call_half_way(ps, scorer, what):
     """A failed HIP call of the program itself, whose error nobody read: a call
