@@ -1401,16 +1401,15 @@ static bool req_ok_host(const ps_req& q, int64_t pool_len) {
          q.tail_len <= pool_len - q.tail_off && (int64_t)q.pre_len + q.tail_len <= PS_MAX_CHAIN;
 }
 
-// Batches of no more requests than this are not worth their 17 launches: 512
-// requests on 16 instances, chains of 130 blocks, take 7.5 ms eight at a time and
-// 17.9 two at a time, where the in-order scheduler, which takes as many per three
-// launches, needs 7.0 and 9.4 ms; sixteen at a time the batches win (4.8; in order 6.4 even
-// with 32).
-// Its insertions grow with the chains: at 2,300 blocks on 64 instances (2,048) it
-// needs 25.2 (34.7) ms two at a time and 16.9 (20.6) eight at a time, the batches
-// 34.3 (38.6) and 13.5 (14.8); four at a time they are even.
-constexpr int32_t kSchedMinBatch = 4, kSchedMinBatchShort = 8;
-constexpr size_t kSchedShortChain = 1024;  // blocks (mean of the window)
+// Batches of no more requests than this are not worth their 17 launches (mean:
+// blocks per chain): the in-order scheduler takes as many requests per three
+// launches, but inserts and walks each chain with one workgroup.  Microseconds a
+// request, batches / in order, of 1, 2 and 4 requests at 512, 2,048, 8,192 and
+// 65,536 blocks on 16 instances: 97 67 47 / 52 42 36, 117 73 49 / 86 71 64,
+// 124 78 51 / 125 93 78, 254 153 101 / 848 598 472 (512 instances: 117 77 52 /
+// 72 51 40, 135 83 54 / 94 67 53, 145 88 56 / 145 101 79, 288 175 116 / 991 677
+// 538); at 130 blocks 8 requests are even (14.7 / 13.7), at 16 the batches win.
+static uint32_t sched_min_batch(size_t mean) { return (uint32_t)std::min<size_t>(8, 8192 / mean); }
 
 // Algorithm 1 per arrival in batches (ps_schedule.hip) of at most `rows`
 // requests, whose hits the context holds; *taken: requests scheduled.  All of
@@ -1438,7 +1437,7 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
   // the budget: per request a row of hits and one of walks, per position the
   // blocks' set
   const size_t row = (size_t)sched_row_stride(ni) * sizeof(uint32_t);
-  const size_t mean = (size_t)(total / n_req + 1);
+  const size_t mean = (size_t)std::max<int64_t>(1, total / n_req);
   const uint32_t max_n =
       (uint32_t)std::max<size_t>(1, std::min<size_t>(rows, c->seq_budget / (2 * row + mean * kCommitPosBytes)));
   const size_t hits = (size_t)max_n * row;
@@ -1451,7 +1450,7 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
   }
   if (room < longest) return PS_OK;
   const uint32_t max_pos = (uint32_t)std::max(longest, std::min({most, c->max_pos, room}));
-  const uint32_t min_batch = (uint32_t)(mean < kSchedShortChain ? kSchedMinBatchShort : kSchedMinBatch);
+  const uint32_t min_batch = sched_min_batch(mean);
   if (std::min<size_t>(max_n, max_pos / mean) <= min_batch) return PS_OK;
 
   const size_t ws_commit = ps_commit_ws_bytes(kSpecBatch, kSpecBatch, max_pos);
@@ -1536,7 +1535,7 @@ static ps_status run_batches(ps_ctx* c, const uint64_t* d_pool, int64_t pool_len
   // window is left to the in-order scheduler: a batch of 256, most of whose
   // requests were scored in vain, costs 450 to 850 us and 2.6 us a request
   // taken, the other 15 to 38 us a request.  (A threshold of 24 a batch instead of
-  // 12 to 16 sent a window away whose first batches alone were short: 4.7 -> 10.2
+  // 8 to 16 sent a window away whose first batches alone were short: 4.7 -> 10.2
   // ms for 1,024 requests.)  The first sweep is short, so that a window without
   // long batches loses little.
   uint32_t done = 0;
@@ -1596,7 +1595,7 @@ static ps_status run_sequential(ps_ctx* c, const uint64_t* d_pool, int64_t pool_
     c->spec_cap = rows;
   }
   int32_t r_first = 0;
-  if (spec && rows > kSchedMinBatch) {
+  if (spec) {
     const ps_status st =
         run_batches(c, d_pool, pool_len, d_reqs, n_req, (uint32_t)rows, d_out, d_sizes, &r_first, s);
     if (st != PS_OK) return st;
